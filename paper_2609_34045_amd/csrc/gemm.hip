@@ -9,10 +9,12 @@
 //     from LDS for 32 MFMAs.  Two waves per SIMD let one issue MFMAs while the
 //     other waits on LDS or the barrier (four waves of 128 x 128 measured 4-5%
 //     slower);
-//   * the SwiGLU projection takes 256 x 224 tiles when they fill whole rounds
-//     of the 256 CUs in fewer tile-times (the 70B gate/up shape: 512 tiles in
-//     2 rounds, against 448 of 256 x 256 whose second round is three quarters
-//     full): eight waves of 64 x 128 and 64 x 96, one of each per SIMD;
+//   * narrower tiles (224, 160 or 128 columns) where they fill whole rounds of
+//     the 256 CUs in less time (the 70B gate/up shape: 512 tiles of 224 columns
+//     in 2 rounds, against 448 of 256 whose second round is three quarters
+//     full): eight waves, the wide and the narrow ones one of each per SIMD;
+//   * up to 128 rows, where the stream of the weights bounds the product, tiles
+//     of 32, 64 or 128 rows in a kernel of their own (gemm_rows_kernel);
 //   * operands go from global memory straight into LDS rings with
 //     global_load_lds (no register staging).  A 64-deep K step makes each load
 //     instruction fetch 8 rows x 128 B, i.e. whole cache lines; 32-deep steps
@@ -25,9 +27,10 @@
 //     bank conflicts;
 //   * each wave reads the fragments of the next 16-wide K slice while the
 //     MFMAs of the current one run;
-//   * narrow projections (few 256-wide column tiles) are split along K over
-//     several workgroups so that the grid covers the 256 CUs; the slices are
-//     stored whole for the consuming kernel to add in order (kGemmPartialF32).
+//   * a product without enough tiles is split along K over several workgroups
+//     so that the grid covers the 256 CUs; the slices are stored whole for the
+//     consuming kernel to add in order (kGemmPartialF32).  gemm_plan chooses
+//     the tile and the slices.
 // Operand fragment layout of v_mfma_f32_32x32x16_f16 (lane l of 64):
 //   A: row l%32, k = 8*(l/32) .. +7      B: column l%32, k = 8*(l/32) .. +7
 //   D: element v (0..15) at row 8*(v/4) + 4*(l/32) + v%4, column l%32
@@ -50,9 +53,6 @@ static_assert(BK == 32 || BK == 64, "K step");
 constexpr int kGemmThreads = 512;  // eight waves, two per SIMD
 #ifndef KF_GEMM_READS_PER_SLOT
 #define KF_GEMM_READS_PER_SLOT 1  // fragment reads issued per MFMA slot
-#endif
-#ifndef KF_GEMM_SPLIT_FLOOR
-#define KF_GEMM_SPLIT_FLOOR 1  // K slices per tile: floor (1) or ceiling (0) of 256 / tiles
 #endif
 #ifndef KF_GEMM_STAGES
 #define KF_GEMM_STAGES (BK == 32 ? 4 : 2)
@@ -112,6 +112,56 @@ struct Params {
 
 constexpr int NW = 8;                        // waves per workgroup
 constexpr int LOADS = TILE_BYTES / 1024 / NW;  // 1 KB direct loads per wave per operand per stage
+
+// Epilogue of one wave's accumulators: MB 32-row blocks from output row row0
+// times JW 32-column blocks from block bw0 of the tile at column n0.  Lane l
+// holds column l % 32 of each block.
+template <int EPI, int MB, int JW>
+__device__ __forceinline__ void store_tile(const Params& p, const f32x16 (&acc)[MB][JW], int lane, int row0, int n0,
+                                           int bw0, int ks) {
+  const int rl = lane & 31, rq = 4 * (lane >> 5);
+  if (EPI == kGemmSwiGLU) {
+    // Each 32-column block holds 16 outputs: columns 0-15 their gate rows,
+    // 16-31 their up rows.  Lanes c and c ^ 16 exchange values; the gate lane
+    // writes elements v = 0..7 of the pair, the up lane v = 8..15.
+    bool bad = false;
+    const bool gl = (lane & 16) == 0;
+    const int nout = p.N >> 1;
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+      for (int j = 0; j < JW; ++j) {
+        float pr[16];
+#pragma unroll
+        for (int v = 0; v < 16; ++v) pr[v] = __shfl_xor(acc[i][j][v], 16);
+        const int col = (n0 >> 1) + 16 * (bw0 + j) + (lane & 15);
+#pragma unroll
+        for (int v = 0; v < 8; ++v) {
+          const int vv = gl ? v : v + 8;
+          const float g = gl ? acc[i][j][v] : pr[v + 8], u = gl ? pr[v] : acc[i][j][v + 8];
+          const int row = row0 + 32 * i + 8 * (vv >> 2) + rq + (vv & 3);
+          if (row < p.M && col < nout) p.Cb[(int64_t)row * nout + col] = f16_checked(g / (1.0f + expf(-g)) * u, bad);
+        }
+      }
+    raise_err(p.err_flag, bad, kErrF16Range);
+  } else {
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const int row = row0 + 32 * i + 8 * (v >> 2) + rq + (v & 3);
+        if (row >= p.M) continue;
+#pragma unroll
+        for (int j = 0; j < JW; ++j) {
+          const int col = n0 + 32 * (bw0 + j) + rl;
+          if (col >= p.N) continue;
+          float* c = p.C + (int64_t)row * p.N + col;
+          if (EPI == kGemmResidF32) *c += acc[i][j][v];
+          else c[(int64_t)ks * p.M * p.N] = acc[i][j][v];
+        }
+      }
+  }
+}
 
 // One wave's share of a tile: the K loop and the epilogue for MB 32-row A
 // blocks from tile row am0 times JW 32-column W blocks from block bw0.  Every
@@ -231,53 +281,11 @@ __device__ __forceinline__ void gemm_wave(const Params& p, uint8_t* smem, const 
   }
   wait_vm<0>();  // no load may still be writing LDS when the workgroup ends
 
-  // Epilogue.  Lane l holds column l % 32 of each block.
-  const int rq = 4 * (lane >> 5);
-  if (EPI == kGemmSwiGLU) {
-    // Each 32-column block holds 16 outputs: columns 0-15 their gate rows,
-    // 16-31 their up rows.  Lanes c and c ^ 16 exchange values; the gate lane
-    // writes elements v = 0..7 of the pair, the up lane v = 8..15.
-    bool bad = false;
-    const bool gl = (lane & 16) == 0;
-    const int nout = p.N >> 1;
-#pragma unroll
-    for (int i = 0; i < MB; ++i)
-#pragma unroll
-      for (int j = 0; j < JW; ++j) {
-        float pr[16];
-#pragma unroll
-        for (int v = 0; v < 16; ++v) pr[v] = __shfl_xor(acc[i][j][v], 16);
-        const int col = (n0 >> 1) + 16 * (bw0 + j) + (lane & 15);
-#pragma unroll
-        for (int v = 0; v < 8; ++v) {
-          const int vv = gl ? v : v + 8;
-          const float g = gl ? acc[i][j][v] : pr[v + 8], u = gl ? pr[v] : acc[i][j][v + 8];
-          const int row = m0 + am0 + 32 * i + 8 * (vv >> 2) + rq + (vv & 3);
-          if (row < p.M && col < nout) p.Cb[(int64_t)row * nout + col] = f16_checked(g / (1.0f + expf(-g)) * u, bad);
-        }
-      }
-    raise_err(p.err_flag, bad, kErrF16Range);
-  } else {
-#pragma unroll
-    for (int i = 0; i < MB; ++i)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int row = m0 + am0 + 32 * i + 8 * (v >> 2) + rq + (v & 3);
-        if (row >= p.M) continue;
-#pragma unroll
-        for (int j = 0; j < JW; ++j) {
-          const int col = n0 + 32 * (bw0 + j) + rl;
-          if (col >= p.N) continue;
-          float* c = p.C + (int64_t)row * p.N + col;
-          if (EPI == kGemmResidF32) *c += acc[i][j][v];
-          else c[(int64_t)ks * p.M * p.N] = acc[i][j][v];
-        }
-      }
-  }
+  store_tile<EPI, MB, JW>(p, acc, lane, m0 + am0, n0, bw0, ks);
 }
 
 // Tiles of 256 rows x 32 NB columns (NB = 8; 7, 5 or 4 where narrower tiles
-// fill the chip in fewer tile-times: see gemm_tile_blocks).  With NB = 8 the
+// fill the chip in less time: see gemm_plan).  With NB = 8 the
 // eight waves are 2 x 4 of 128 x 64; with NB = 7 (5) they are 4 x 2 of 64 x 128
 // (96) and 64 x 96 (64), so that with waves dealt to the SIMDs round-robin each
 // SIMD holds one of each; with NB = 4, 4 x 2 of 64 x 64.  The W tile is loaded
@@ -360,95 +368,214 @@ __global__ __launch_bounds__(kGemmThreads) void gemm256_kernel(const Params p) {
   }
 }
 
-}  // namespace
+// ------------------------------------------------------------------ few rows
+// Products over up to 128 rows: bound by the stream of the weights from HBM,
+// not by the matrix cores, so the tile is only as tall as the rows (32, 64 or
+// 128) and the launch is cut along N and K until every CU streams.  A
+// workgroup of WM x WN waves, each with MBW x JW blocks of 32 x 32, takes
+// 32 MBW WM rows x 32 JW WN columns of one K slice; both operands go straight
+// into one LDS ring of D stages of 64-deep K steps (loads run D - 1 steps
+// ahead).  Up to 64 rows the ring leaves room for two workgroups on a CU, so
+// one computes while the other waits; at 128 rows, where each weight fragment
+// meets four times the products, eight waves share the tile instead.
+// Against 256-row tiles (weights cold in HBM, 8B shape): 32 rows, gate/up
+// 87 -> 39 us (6.0 TB/s), QKV 34.5 -> 11, output 32 -> 8.4, down 40 -> 20; 64
+// rows 89 -> 42, 34 -> 12, 33 -> 9.6, 41 -> 22; 128 rows 90 -> 50, 34 -> 16,
+// 33 -> 14, 43 -> 31.  Tried and no faster: deeper rings (6 stages), 128-deep K
+// steps, 64-column tiles, four waves of 64 x 64 at 128 rows.
+template <int EPI, int MBW, int JW, int WM, int WN, int D>
+__global__ __launch_bounds__(64 * WM * WN) void gemm_rows_kernel(const Params p) {
+  constexpr int NWV = WM * WN;                          // waves
+  constexpr int KS = 64;                                // K step
+  constexpr int TM = 32 * MBW * WM, TN = 32 * JW * WN;  // tile rows and columns
+  constexpr int RB = KS * 2, CPR = RB / 16;             // bytes and 16-byte chunks of a tile row per step
+  constexpr int RPL = 64 / CPR;                         // tile rows per 1 KB load
+  constexpr int LA = TM * RB / 1024 / NWV, LW = TN * RB / 1024 / NWV;  // 1 KB loads per wave and stage
+  constexpr int NL = LA + LW, STAGE = (TM + TN) * RB;
+  static_assert(LA >= 1 && LW >= 1 && D >= 2 && (D - 2) * NL < 64, "loads in flight");
+  static_assert(D * STAGE <= 160 * 1024, "LDS");
+  __shared__ __attribute__((aligned(1024))) uint8_t smem[D * STAGE];
 
-#ifndef KF_GEMM_MAX_SPLIT
-#define KF_GEMM_MAX_SPLIT 8  // upper bound on K slices per output tile
-#endif
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int mt = (p.M + TM - 1) / TM;
+  const int bid = blockIdx.x;
+  const int ks = bid % p.splitk, t = bid / p.splitk;
+  const int m0 = (t % mt) * TM, n0 = (t / mt) * TN;
+  const int K = p.K, nk_all = K / KS;
+  const int k_begin = (int)((int64_t)nk_all * ks / p.splitk), k_end = (int)((int64_t)nk_all * (ks + 1) / p.splitk);
+  const int nk = k_end - k_begin;
 
-// K slices for tiles of 32 nb columns.
-static int splitk_for(int M, int N, int K, int nb) {
-  const int tiles = ((M + BM - 1) / BM) * ((N + 32 * nb - 1) / (32 * nb));
-  const int k32 = K / 32;
-  if (tiles >= 192 || k32 < 128) return 1;  // enough tiles, or a short (cheap) reduction
-  int s = KF_GEMM_SPLIT_FLOOR ? 256 / tiles : (256 + tiles - 1) / tiles;
-  if (s > k32 / 64) s = k32 / 64;  // keep at least 2048 of K per slice
-  if (s > KF_GEMM_MAX_SPLIT) s = KF_GEMM_MAX_SPLIT;
-  return s < 1 ? 1 : s;
+  // Load j of this wave fills the RPL tile rows RPL (NWV j + wave) ..; lane l writes
+  // slot l % CPR of row l / CPR and fetches the chunk that belongs there.
+  const int w_rows = EPI == kGemmSwiGLU ? (p.N >> 1) : p.N;
+  const uint16_t* asrc[LA];
+  const uint16_t* wsrc[LW];
+  auto rswz = [](int r) { return (r & 7) ^ ((r >> 3) & 1); };
+  auto chunk = [&](int r) { return ((lane & (CPR - 1)) ^ rswz(r)) * 8 + k_begin * KS; };
+#pragma unroll
+  for (int j = 0; j < LA; ++j) {
+    const int r = RPL * (NWV * j + wave) + lane / CPR;
+    asrc[j] = p.A + (int64_t)min(m0 + r, p.M - 1) * K + chunk(r);  // rows past M repeat the last; never stored
+  }
+#pragma unroll
+  for (int j = 0; j < LW; ++j) {
+    const int r = RPL * (NWV * j + wave) + lane / CPR;
+    // SwiGLU: each 32-row block holds 16 gate rows, then the 16 up rows of the same outputs
+    const int wr = EPI == kGemmSwiGLU ? (n0 >> 1) + 16 * (r >> 5) + (r & 15) : n0 + r;
+    const uint16_t* wb = EPI == kGemmSwiGLU && (r & 16) ? p.W2 : p.W;
+    wsrc[j] = wb + (int64_t)min(wr, w_rows - 1) * K + chunk(r);  // rows past N repeat the last; never stored
+  }
+  // Workgroups of an unsplit launch walk K from starts of their own, wrapping
+  // around, as do those whose slices begin at multiples of 4 KB within a row: all
+  // at the same offset of rows a power of two apart, they press on a few memory
+  // channels at a time (8B-shaped gate/up over 32 rows: 50.9 -> 40.7 us, with the
+  // weights loaded non-temporally; 64 rows 53.3 -> 44.2).
+  const int rot = p.splitk == 1 || (nk * RB) % 4096 == 0 ? (int)(((unsigned)t * 13u) % (unsigned)nk) : 0;
+  auto issue = [&](int k) {
+    uint8_t* st = smem + (k % D) * STAGE;
+    const int kk = k + rot < nk ? k + rot : k + rot - nk;
+#pragma unroll
+    for (int j = 0; j < LA; ++j) {
+      const uint16_t* src = asrc[j] + (int64_t)kk * KS;
+      uint8_t* dst = st + 1024 * (NWV * j + wave);
+      __builtin_amdgcn_global_load_lds(src, (lds_ptr)dst, 16, 0, 0);
+    }
+#pragma unroll
+    for (int j = 0; j < LW; ++j) {
+      const uint16_t* src = wsrc[j] + (int64_t)kk * KS;
+      uint8_t* dst = st + TM * RB + 1024 * (NWV * j + wave);
+      __builtin_amdgcn_global_load_lds(src, (lds_ptr)dst, 16, 0, 2);  // non-temporal: read once
+    }
+  };
+
+  f32x16 acc[MBW][JW];
+#pragma unroll
+  for (int i = 0; i < MBW; ++i)
+#pragma unroll
+    for (int j = 0; j < JW; ++j)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+
+  const int wm = wave / WN, wn = wave % WN;
+  const int rl = lane & 31, kh = lane >> 5;
+  int aoff[MBW], woff[JW];
+#pragma unroll
+  for (int i = 0; i < MBW; ++i) aoff[i] = (32 * (MBW * wm + i) + rl) * RB;
+#pragma unroll
+  for (int j = 0; j < JW; ++j) woff[j] = (TM + 32 * (JW * wn + j) + rl) * RB;
+  const int f = rswz(rl);  // the row swizzle depends on the row's low four bits only
+
+#pragma unroll
+  for (int s = 0; s < D - 1; ++s)
+    if (s < nk) issue(s);
+  for (int k = 0; k < nk; ++k) {
+    // step k has landed once only the later steps' loads are in flight
+    const int later = nk - 1 - k;
+    if (later >= D - 2) wait_vm<(D - 2) * NL>();
+    else if (D > 3 && later == D - 3) wait_vm<(D > 3 ? D - 3 : 0) * NL>();
+    else if (D > 4 && later == D - 4) wait_vm<(D > 4 ? D - 4 : 0) * NL>();
+    else wait_vm<0>();
+    // Every wave's loads of step k have landed, and every wave's reads of step
+    // k - 1 have returned (their products were issued), so its stage takes step
+    // k + D - 1.
+    block_barrier();
+    if (k + D - 1 < nk) issue(k + D - 1);
+    const uint8_t* st = smem + (k % D) * STAGE;
+#pragma unroll
+    for (int s = 0; s < KS / 16; ++s) {
+      const int c = ((2 * s + kh) ^ f) * 16;
+      v4u fa[MBW], fw[JW];
+#pragma unroll
+      for (int j = 0; j < JW; ++j) fw[j] = *reinterpret_cast<const v4u*>(st + woff[j] + c);
+#pragma unroll
+      for (int i = 0; i < MBW; ++i) fa[i] = *reinterpret_cast<const v4u*>(st + aoff[i] + c);
+#pragma unroll
+      for (int i = 0; i < MBW; ++i)
+#pragma unroll
+        for (int j = 0; j < JW; ++j) acc[i][j] = mfma32(fa[i], fw[j], acc[i][j]);
+    }
+    wait_lds();  // no read of this step's stage is in flight past the next barrier
+  }
+  store_tile<EPI, MBW, JW>(p, acc, lane, m0 + 32 * MBW * wm, n0, JW * wn, ks);
 }
 
-#ifndef KF_GEMM_NARROW
-#define KF_GEMM_NARROW 1  // split-K tiles of 160 or 128 columns where they take fewer tile-times
-#endif
-#ifndef KF_GEMM_NARROW_COST
-#define KF_GEMM_NARROW_COST 13  // cost of a narrow tile's column-step, in tenths of a 256-column tile's
-#endif
-// Tile width of the split-K (partial-sum) launch: the number of 32-column
-// blocks (8, 5 or 4) whose grid, tiles x K slices, takes the fewest
-// tile-times over the 256 CUs.  A tile-time is its columns times its K steps,
-// weighted 1.3x for the narrow tiles: per column-step they measured 1.12-1.34x
-// the 256-column tile's (fewer MFMAs per fragment read, and a fuller chip runs
-// at a lower clock).  The Qwen3-32B-shaped QKV and output projections (160 of
-// the 256 CUs busy with 256-column tiles) gain: 69.4 -> 59.4 and 57.9 -> 48.5 us
-// with 160-column tiles, where the unweighted rule's 160-column tiles for its
-// down projection (240 workgroups either way) lost 122 -> 140 us and for the
-// 70B-shaped QKV projection 83.6 -> 87.3 us.
-static int partial_tile_blocks(int M, int N, int K) {
-  if (!KF_GEMM_NARROW) return 8;
-  const int mt = (M + BM - 1) / BM, nk = K / BK;
-  int best = 8;
-  int64_t best_cost = 0;
-  for (int nb : {8, 5, 4}) {
-    const int s = splitk_for(M, N, K, nb);
-    const int64_t wgs = (int64_t)mt * ((N + 32 * nb - 1) / (32 * nb)) * s;
-    const int64_t cost = (wgs + 255) / 256 * nb * ((nk + s - 1) / s) * (nb == 8 ? 10 : KF_GEMM_NARROW_COST);
-    if (nb == 8 || cost < best_cost) {
-      best = nb;
-      best_cost = cost;
+}  // namespace
+
+// ------------------------------------------------------------------ launch plan
+// Workgroup tiles and the time of a 64-deep K step of one of them with a tile on
+// every CU, measured over the projections of the 8B, 32B, 70B and Qwen3 shapes
+// at 20 to 2048 rows (us; the step of a small tile is the wait for its weights).
+struct Tile {
+  int rows, cols;
+  float step_us;
+  bool few;  // gemm_rows_kernel (few rows), else gemm256_kernel
+};
+static constexpr Tile kTiles[] = {
+    {32, 128, 0.58f, true}, {64, 128, 0.64f, true}, {128, 128, 0.78f, true}, {128, 256, 1.17f, true},
+    {256, 128, 1.15f, false}, {256, 160, 1.35f, false}, {256, 224, 1.55f, false}, {256, 256, 1.75f, false},
+};
+
+// The tile and K slices of least estimated time: whole rounds of the 256 CUs
+// times a slice's K steps, 4 us for the launch, its first loads and its
+// stores, and for each slice of a split product 8 bytes per value (written
+// here, read by the consumer) at 6 TB/s.  At most eight slices (the consumers
+// add no more), of at least four steps, and no more than part_elems holds.
+// Over eighteen projections of the shapes above at 20, 64, 128, 200, 512 and 2048
+// rows the choice is the fastest of all tiles and slices or within 8% of it,
+// bar three at H = 8192 (10%).
+GemmPlan gemm_plan(int epi, int M, int N, int K, int64_t part_elems) {
+  GemmPlan best{7, 1};
+  float best_us = 0.f;
+  const int nk = K / BK;
+  for (int t = 0; t < (int)(sizeof(kTiles) / sizeof(kTiles[0])); ++t) {
+    const Tile& T = kTiles[t];
+    if (T.few && M > 128) continue;
+    const int64_t tiles = (int64_t)((M + T.rows - 1) / T.rows) * ((N + T.cols - 1) / T.cols);
+    for (int s = 1; s <= kGemmMaxSlices && s <= nk / 4; ++s) {
+      if (s > 1 && (epi == kGemmSwiGLU || (int64_t)s * M * N > part_elems)) break;
+      const float us = (float)((tiles * s + 255) / 256) * ((nk + s - 1) / s) * T.step_us + 4.f +
+                       (s > 1 ? s : 0) * (float)M * N * 8e-6f / 6.f;
+      if (best_us == 0.f || us < best_us) {
+        best_us = us;
+        best = GemmPlan{t, s};
+      }
     }
   }
   return best;
 }
 
-int gemm_splitk(int M, int N, int K) { return splitk_for(M, N, K, partial_tile_blocks(M, N, K)); }
-
-// 32-column blocks per tile: for the split-K launch see partial_tile_blocks;
-// 7 for the SwiGLU launch when 224-column tiles take fewer tile-times than
-// 256-column ones over whole rounds of the 256 CUs (70B gate/up: 512 tiles of 7
-// blocks in 2 rounds against 448 of 8, the second round three quarters full);
-// else 8.
-int gemm_tile_blocks(int epi, int M, int N, int K) {
-  if (epi == kGemmPartialF32) return partial_tile_blocks(M, N, K);
-  if (epi != kGemmSwiGLU) return 8;
-  const int mt = (M + BM - 1) / BM;
-  auto cost = [&](int nb) { return ((mt * ((N + 32 * nb - 1) / (32 * nb)) + 255) / 256) * nb; };
-  return cost(7) < cost(8) ? 7 : 8;
-}
-
-hipError_t launch_gemm(int epi, const uint16_t* A, const uint16_t* W, const uint16_t* W2, int M, int N, int K,
-                       float* C, uint16_t* Cb, int* err_flag, hipStream_t s) {
-  if (M <= 0 || N <= 0 || K <= 0 || K % BK) return hipErrorInvalidValue;
-  if (epi == kGemmSwiGLU && N % 32) return hipErrorInvalidValue;  // whole 16-output gate/up blocks
-  // the nonlinearity and the residual update need complete sums: only the partial epilogue splits K
-  Params p{A, W, W2, M, N, K, epi == kGemmPartialF32 ? gemm_splitk(M, N, K) : 1, C, Cb, err_flag};
-  const int nb = gemm_tile_blocks(epi, M, N, K);
-  const int grid = ((M + BM - 1) / BM) * ((N + 32 * nb - 1) / (32 * nb)) * p.splitk;
-  switch (epi) {
-    case kGemmResidF32:
-      hipLaunchKernelGGL((gemm256_kernel<kGemmResidF32, 8>), dim3(grid), dim3(kGemmThreads), 0, s, p);
-      break;
-    case kGemmSwiGLU:
-      if (nb == 7) hipLaunchKernelGGL((gemm256_kernel<kGemmSwiGLU, 7>), dim3(grid), dim3(kGemmThreads), 0, s, p);
-      else hipLaunchKernelGGL((gemm256_kernel<kGemmSwiGLU, 8>), dim3(grid), dim3(kGemmThreads), 0, s, p);
-      break;
-    case kGemmPartialF32:
-      if (nb == 5) hipLaunchKernelGGL((gemm256_kernel<kGemmPartialF32, 5>), dim3(grid), dim3(kGemmThreads), 0, s, p);
-      else if (nb == 4) hipLaunchKernelGGL((gemm256_kernel<kGemmPartialF32, 4>), dim3(grid), dim3(kGemmThreads), 0, s, p);
-      else hipLaunchKernelGGL((gemm256_kernel<kGemmPartialF32, 8>), dim3(grid), dim3(kGemmThreads), 0, s, p);
-      break;
+template <int EPI>
+static hipError_t launch_tile(const Params& p, int tile, hipStream_t s) {
+  const Tile& T = kTiles[tile];
+  const dim3 grid((unsigned)((int64_t)((p.M + T.rows - 1) / T.rows) * ((p.N + T.cols - 1) / T.cols) * p.splitk));
+  switch (tile) {
+    case 0: hipLaunchKernelGGL((gemm_rows_kernel<EPI, 1, 1, 1, 4, 4>), grid, dim3(256), 0, s, p); break;
+    case 1: hipLaunchKernelGGL((gemm_rows_kernel<EPI, 2, 1, 1, 4, 3>), grid, dim3(256), 0, s, p); break;
+    case 2: hipLaunchKernelGGL((gemm_rows_kernel<EPI, 2, 1, 2, 4, 4>), grid, dim3(512), 0, s, p); break;
+    case 3: hipLaunchKernelGGL((gemm_rows_kernel<EPI, 2, 2, 2, 4, 3>), grid, dim3(512), 0, s, p); break;
+    case 4: hipLaunchKernelGGL((gemm256_kernel<EPI, 4>), grid, dim3(kGemmThreads), 0, s, p); break;
+    case 5: hipLaunchKernelGGL((gemm256_kernel<EPI, 5>), grid, dim3(kGemmThreads), 0, s, p); break;
+    case 6: hipLaunchKernelGGL((gemm256_kernel<EPI, 7>), grid, dim3(kGemmThreads), 0, s, p); break;
+    case 7: hipLaunchKernelGGL((gemm256_kernel<EPI, 8>), grid, dim3(kGemmThreads), 0, s, p); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
+}
+
+hipError_t launch_gemm(int epi, const GemmPlan& plan, const uint16_t* A, const uint16_t* W, const uint16_t* W2, int M,
+                       int N, int K, float* C, uint16_t* Cb, int* err_flag, hipStream_t s) {
+  if (M <= 0 || N <= 0 || K <= 0 || K % BK || plan.slices < 1 || plan.slices > K / BK) return hipErrorInvalidValue;
+  if (epi == kGemmSwiGLU && N % 32) return hipErrorInvalidValue;  // whole 16-output gate/up blocks
+  // the nonlinearity and the residual update need complete sums: only the partial epilogue splits K
+  if (epi != kGemmPartialF32 && plan.slices != 1) return hipErrorInvalidValue;
+  const Params p{A, W, W2, M, N, K, plan.slices, C, Cb, err_flag};
+  switch (epi) {
+    case kGemmResidF32: return launch_tile<kGemmResidF32>(p, plan.tile, s);
+    case kGemmSwiGLU: return launch_tile<kGemmSwiGLU>(p, plan.tile, s);
+    case kGemmPartialF32: return launch_tile<kGemmPartialF32>(p, plan.tile, s);
+    default: return hipErrorInvalidValue;
+  }
 }
 
 }  // namespace kf

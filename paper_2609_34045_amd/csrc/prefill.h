@@ -29,37 +29,48 @@ struct PrefillLayer {
   int out_bf16;
 };
 
-// Device workspace, grown on demand to the largest chunk seen.
+// Matrix-core GEMM of the prefill projections (gemm.hip); K must be a multiple
+// of 64 (the stage's hidden, ffn and query widths are), else hipErrorInvalidValue.
+//   kGemmResidF32   C[M][N] += A W^T (unsplit; the residual stream)
+//   kGemmSwiGLU     Cb[M][N/2] = silu(gate) * up in fp16, W the gate rows and W2 the up rows
+//   kGemmPartialF32 K slice ks to C + ks*M*N (plain stores); the consumer adds the
+//                   plan's slices in order
+enum GemmEpi : int { kGemmResidF32 = 1, kGemmSwiGLU = 2, kGemmPartialF32 = 3 };
+constexpr int kGemmMaxSlices = 8;  // K slices that the consuming kernels add
+// Tile shape and K slices of one product.  `part_elems`: fp32 values that the slices may take.
+struct GemmPlan {
+  int tile, slices;
+};
+GemmPlan gemm_plan(int epi, int M, int N, int K, int64_t part_elems);
+hipError_t launch_gemm(int epi, const GemmPlan& plan, const uint16_t* A, const uint16_t* W, const uint16_t* W2, int M,
+                       int N, int K, float* C, uint16_t* Cb, int* err_flag, hipStream_t s);
+
+// Device workspace, grown on demand to the largest chunk seen and laid out anew for each chunk.
 struct PrefillWorkspace {
-  int cap_T = 0;
+  int64_t cap = 0;  // bytes at mem
   char* mem = nullptr;
   float* x = nullptr;      // [T][H] residual stream
   uint16_t* xn = nullptr;  // [T][H] normalised, fp16
-  float* part = nullptr;   // split-K partial sums [slices][T][N] of the last split projection
+  float* part = nullptr;   // split-K partial sums [slices][T][N] of the last split projection, or attention partials
+  int64_t part_elems = 0;  // values at part
+  GemmPlan qkv, oproj, gateup, down;  // the chunk's projections
   int pending = 0;         // slices of the down projection in `part` not yet added to x
   uint16_t* q = nullptr;   // [T][nq][hd] rotated queries, fp16
   uint16_t* o = nullptr;   // [T][nq hd] attention output, fp16
   uint16_t* act = nullptr; // [T][F] SwiGLU output, fp16
 };
 
-// Grows ws (hipMalloc) to hold a chunk of a.T tokens.
+// Bytes of the no-allocation prefill's scratch array (a 512-token chunk of the 70B shape needs 132 MiB).
+constexpr int64_t kPrefillScratchBytes = 144LL << 20;
+
+// Grows ws (hipMalloc) to hold a chunk of a.T tokens and lays it out.
 hipError_t prefill_reserve(PrefillWorkspace& ws, const PrefillArgs& a);
 void prefill_free(PrefillWorkspace& ws);
-// Device bytes a chunk of a.T tokens needs, and the workspace laid out from `base`
-// (at least that many bytes, 256-byte aligned; ws does not own it).
+// Device bytes a chunk of a.T tokens needs at least; a chunk that needs no more than
+// kPrefillScratchBytes can be laid out in that many bytes at `base` (256-byte
+// aligned; ws does not own them).
 int64_t prefill_ws_bytes(const PrefillArgs& a);
 void prefill_carve(PrefillWorkspace& ws, char* base, const PrefillArgs& a);
 hipError_t prefill_layer(PrefillWorkspace& ws, const PrefillArgs& a, const PrefillLayer& l, const Tracer& tr);
-
-// Matrix-core GEMM of the prefill projections (gemm.hip); K must be a multiple
-// of 64 (the stage's hidden, ffn and query widths are), else hipErrorInvalidValue.
-//   kGemmResidF32   C[M][N] += A W^T (unsplit; the residual stream)
-//   kGemmSwiGLU     Cb[M][N/2] = silu(gate) * up in fp16, W the gate rows and W2 the up rows
-//   kGemmPartialF32 K slice ks to C + ks*M*N (plain stores); the consumer adds the
-//                   gemm_splitk(M, N, K) slices in order
-enum GemmEpi : int { kGemmResidF32 = 1, kGemmSwiGLU = 2, kGemmPartialF32 = 3 };
-int gemm_splitk(int M, int N, int K);
-hipError_t launch_gemm(int epi, const uint16_t* A, const uint16_t* W, const uint16_t* W2, int M, int N, int K,
-                       float* C, uint16_t* Cb, int* err_flag, hipStream_t s);
 
 }  // namespace kf

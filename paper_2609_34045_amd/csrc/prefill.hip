@@ -63,7 +63,7 @@ __device__ __forceinline__ f32x16 mfma32(v4u a, v4u b, f32x16 c) {
 // Threads move 16 bytes at a time and request every slice before adding; the
 // row loops are unrolled by 4, so the loads of four 16-byte steps are in flight
 // together (70B-shaped rows: 24.6 -> 21.1 us per norm).
-constexpr int kMaxSlices = 8;
+constexpr int kMaxSlices = kGemmMaxSlices;
 #ifndef KF_PF_ATTN_SPLIT
 #define KF_PF_ATTN_SPLIT 2  // key splits of the prefill attention when the chunk gives < 512 workgroups
 #endif
@@ -694,64 +694,115 @@ void prefill_free(PrefillWorkspace& ws) {
   ws = PrefillWorkspace{};
 }
 
-// Bytes of each workspace buffer for a chunk of a.T tokens, in layout order:
-// x, xn, part, q, o, act.
-static void prefill_sizes(const PrefillArgs& a, int64_t (&sz)[6]) {
-  const int64_t T = a.T, H = a.H, nqkv = (int64_t)(a.nq + 2 * a.nkv) * a.hd;
-  // the split-K slices of the largest of the QKV, O and down projections
-  const int64_t part_qkv = (int64_t)gemm_splitk(a.T, (int)nqkv, H) * T * nqkv;
-  const int64_t part_o = (int64_t)gemm_splitk(a.T, H, a.nq * a.hd) * T * H;
-  const int64_t part_d = (int64_t)gemm_splitk(a.T, H, a.F) * T * H;
-  const int64_t part_attn = (int64_t)KF_PF_ATTN_SPLIT * T * a.nq * (a.hd + 2);  // key-split attention partials
-  const int64_t part = std::max(std::max(part_qkv, part_attn), std::max(part_o, part_d));
-  sz[0] = a256(T * H * 4);
-  sz[1] = a256(T * H * 2);
-  sz[2] = a256(part * 4);
-  sz[3] = a256(T * a.nq * a.hd * 2);
-  sz[4] = a256(T * a.nq * a.hd * 2);
-  sz[5] = a256(T * a.F * 2);
+// K slices of a split projection that the workspace has always been sized for:
+// tiles of 256 rows x 256, 160 or 128 columns in the fewest tile-times over 256
+// CUs.  The sizes a no-allocation chunk is accepted by rest on this rule, so it
+// stays as it is; which tiles and slices a launch takes is gemm_plan's choice
+// within the space.
+static int sized_slices(int M, int N, int K) {
+  const int mt = (M + 255) / 256, nk = K / 64, k32 = K / 32;
+  int best = 1;
+  int64_t best_cost = 0;
+  for (int nb : {8, 5, 4}) {
+    const int tiles = mt * ((N + 32 * nb - 1) / (32 * nb));
+    int s = 1;
+    if (tiles < 192 && k32 >= 128) s = std::max(1, std::min(std::min(256 / tiles, k32 / 64), kMaxSlices));
+    const int64_t cost = ((int64_t)tiles * s + 255) / 256 * nb * ((nk + s - 1) / s) * (nb == 8 ? 10 : 13);
+    if (nb == 8 || cost < best_cost) {
+      best = s;
+      best_cost = cost;
+    }
+  }
+  return best;
 }
 
-int64_t prefill_ws_bytes(const PrefillArgs& a) {
-  int64_t sz[6];
-  prefill_sizes(a, sz);
-  return sz[0] + sz[1] + sz[2] + sz[3] + sz[4] + sz[5];
+// fp32 values of the partial sums of a chunk of T tokens by that rule: the
+// slices of the largest of the QKV, O and down projections, or two key splits
+// of the attention.
+static int64_t sized_part(const PrefillArgs& a, int64_t T) {
+  const int64_t H = a.H, nqkv = (int64_t)(a.nq + 2 * a.nkv) * a.hd;
+  const int64_t qkv = sized_slices((int)T, (int)nqkv, a.H) * T * nqkv;
+  const int64_t o = sized_slices((int)T, a.H, a.nq * a.hd) * T * H;
+  const int64_t d = sized_slices((int)T, a.H, a.F) * T * H;
+  const int64_t attn = 2 * T * a.nq * (a.hd + 2);
+  return std::max(std::max(qkv, attn), std::max(o, d));
+}
+
+// Bytes of every other buffer, in layout order (x, xn, q, o, act).
+static void other_sizes(const PrefillArgs& a, int64_t (&sz)[5]) {
+  const int64_t T = a.T;
+  sz[0] = a256(T * a.H * 4);
+  sz[1] = a256(T * a.H * 2);
+  sz[2] = a256(T * a.nq * a.hd * 2);
+  sz[3] = a256(T * a.nq * a.hd * 2);
+  sz[4] = a256(T * a.F * 2);
+}
+static int64_t other_bytes(const PrefillArgs& a) {
+  int64_t sz[5];
+  other_sizes(a, sz);
+  return sz[0] + sz[1] + sz[2] + sz[3] + sz[4];
+}
+
+int64_t prefill_ws_bytes(const PrefillArgs& a) { return other_bytes(a) + a256(sized_part(a, a.T) * 4); }
+
+// Space for partial sums that a chunk's plan may use: what the sizing rule
+// gives, raised to kPartSmall for a chunk that fits the scratch array (as far
+// as the array goes, so that the same chunk gets the same plan, and so the
+// same bits, wherever its workspace lies) and to kPartLarge for others.
+constexpr int64_t kPartSmall = 48LL << 20, kPartLarge = 256LL << 20;
+static int64_t part_bytes(const PrefillArgs& a) {
+  const int64_t sized = a256(sized_part(a, a.T) * 4), other = other_bytes(a);
+  if (other + sized > kPrefillScratchBytes) return std::max(sized, kPartLarge);
+  return std::max(sized, std::min(kPartSmall, kPrefillScratchBytes - other));
 }
 
 void prefill_carve(PrefillWorkspace& ws, char* base, const PrefillArgs& a) {
-  int64_t sz[6];
-  prefill_sizes(a, sz);
+  int64_t sz[5];
+  other_sizes(a, sz);
   char* p = base;
   ws.x = (float*)p;
   p += sz[0];
   ws.xn = (uint16_t*)p;
   p += sz[1];
-  ws.part = (float*)p;
-  p += sz[2];
   ws.q = (uint16_t*)p;
-  p += sz[3];
+  p += sz[2];
   ws.o = (uint16_t*)p;
-  p += sz[4];
+  p += sz[3];
   ws.act = (uint16_t*)p;
+  p += sz[4];
+  ws.part = (float*)p;
+  ws.part_elems = part_bytes(a) / 4;
   ws.pending = 0;
+  ws.qkv = gemm_plan(kGemmPartialF32, a.T, (a.nq + 2 * a.nkv) * a.hd, a.H, ws.part_elems);
+  ws.oproj = gemm_plan(kGemmPartialF32, a.T, a.H, a.nq * a.hd, ws.part_elems);
+  ws.gateup = gemm_plan(kGemmSwiGLU, a.T, 2 * a.F, a.H, 0);
+  ws.down = gemm_plan(kGemmPartialF32, a.T, a.H, a.F, ws.part_elems);
 }
 
 hipError_t prefill_reserve(PrefillWorkspace& ws, const PrefillArgs& a) {
-  if (a.T <= ws.cap_T && ws.mem) return hipSuccess;
-  const int64_t total = prefill_ws_bytes(a);
-  char* mem = nullptr;
-  // Drain work that may still use the old buffer before freeing it.
-  hipError_t e = hipStreamSynchronize(a.stream);
-  if (e != hipSuccess) return e;
-  e = hipMalloc((void**)&mem, total);
-  if (e != hipSuccess) {
-    (void)hipGetLastError();
-    return hipErrorOutOfMemory;
+  // A shorter chunk must fit too (a caller may capture one after a longer one
+  // has run).  Its other buffers are smaller; its partial sums may not be: the
+  // slices grow where fewer tokens make fewer row tiles, most at the end of
+  // each 256-token tile.
+  int64_t part = part_bytes(a);
+  PrefillArgs b = a;
+  for (b.T = 256; b.T < a.T; b.T += 256) part = std::max(part, part_bytes(b));
+  const int64_t total = other_bytes(a) + std::max(part, kPartSmall);
+  if (total > ws.cap) {
+    char* mem = nullptr;
+    // Drain work that may still use the old buffer before freeing it.
+    hipError_t e = hipStreamSynchronize(a.stream);
+    if (e != hipSuccess) return e;
+    e = hipMalloc((void**)&mem, total);
+    if (e != hipSuccess) {
+      (void)hipGetLastError();
+      return hipErrorOutOfMemory;
+    }
+    prefill_free(ws);
+    ws.mem = mem;
+    ws.cap = total;
   }
-  prefill_free(ws);
-  ws.mem = mem;
-  ws.cap_T = a.T;
-  prefill_carve(ws, mem, a);
+  prefill_carve(ws, ws.mem, a);
   return hipSuccess;
 }
 
@@ -770,14 +821,11 @@ hipError_t prefill_layer(PrefillWorkspace& ws, const PrefillArgs& a, const Prefi
   ws.pending = 0;
   if ((e = hipGetLastError()) != hipSuccess) return e;
   tr.begin(QKV);
-  const int s_qkv = gemm_splitk(T, nqkv, H);
-  if (s_qkv > kMaxSlices || gemm_splitk(T, H, a.nq * a.hd) > kMaxSlices || gemm_splitk(T, H, a.F) > kMaxSlices)
-    return hipErrorInvalidValue;  // more split-K slices than the consuming kernels add
-  e = launch_gemm(kGemmPartialF32, ws.xn, l.wqkv, nullptr, T, nqkv, H, ws.part, nullptr, a.err_flag, s);
+  e = launch_gemm(kGemmPartialF32, ws.qkv, ws.xn, l.wqkv, nullptr, T, nqkv, H, ws.part, nullptr, a.err_flag, s);
   tr.end(QKV);
   if (e != hipSuccess) return e;
   tr.begin(ROPE);
-  hipLaunchKernelGGL(rope_kv_kernel, dim3(T), dim3(256), 0, s, ws.part, s_qkv, (int64_t)T * nqkv, ws.q, l.kc, l.vc,
+  hipLaunchKernelGGL(rope_kv_kernel, dim3(T), dim3(256), 0, s, ws.part, ws.qkv.slices, (int64_t)T * nqkv, ws.q, l.kc, l.vc,
                      a.kv, a.user, a.rope_cos, a.rope_sin, a.nq, a.nkv, a.hd, a.pos0, l.g_qn, l.g_kn, a.eps,
                      a.err_flag);
   tr.end(ROPE);
@@ -812,27 +860,28 @@ hipError_t prefill_layer(PrefillWorkspace& ws, const PrefillArgs& a, const Prefi
   tr.end(ATTN);
   // O and down: split along K into slices that the next norm (or the output
   // store) adds in order; an unsplit projection adds into x directly.
-  auto resid_proj = [&](int cls, const uint16_t* A, const uint16_t* W, int K, int* pend) {
-    const int sp = gemm_splitk(T, H, K);
+  auto resid_proj = [&](int cls, const GemmPlan& pl, const uint16_t* A, const uint16_t* W, int K, int* pend) {
+    const bool split = pl.slices > 1;
     tr.begin(cls);
-    const hipError_t le = sp > 1 ? launch_gemm(kGemmPartialF32, A, W, nullptr, T, H, K, ws.part, nullptr, a.err_flag, s)
-                                 : launch_gemm(kGemmResidF32, A, W, nullptr, T, H, K, ws.x, nullptr, a.err_flag, s);
+    const hipError_t le = launch_gemm(split ? kGemmPartialF32 : kGemmResidF32, pl, A, W, nullptr, T, H, K,
+                                      split ? ws.part : ws.x, nullptr, a.err_flag, s);
     tr.end(cls);
-    *pend = sp > 1 ? sp : 0;
+    *pend = split ? pl.slices : 0;
     return le;
   };
   int pend_o = 0;
-  if ((e = resid_proj(OPROJ, ws.o, l.wo, a.nq * a.hd, &pend_o)) != hipSuccess) return e;
+  if ((e = resid_proj(OPROJ, ws.oproj, ws.o, l.wo, a.nq * a.hd, &pend_o)) != hipSuccess) return e;
   tr.begin(NORM);
   hipLaunchKernelGGL(rmsnorm_rows_f16_kernel, dim3(T), dim3(256), 0, s, ws.x, ws.part, pend_o, TH, l.g_mlp, a.eps,
                      ws.xn, H, a.err_flag);
   tr.end(NORM);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   tr.begin(GATEUP);
-  e = launch_gemm(kGemmSwiGLU, ws.xn, l.wg, l.wu, T, 2 * a.F, H, nullptr, ws.act, a.err_flag, s);
+  e = launch_gemm(kGemmSwiGLU, ws.gateup, ws.xn, l.wg, l.wu, T, 2 * a.F, H, nullptr,
+                  ws.act, a.err_flag, s);
   tr.end(GATEUP);
   if (e != hipSuccess) return e;
-  if ((e = resid_proj(DOWN, ws.act, l.wd, a.F, &ws.pending)) != hipSuccess) return e;
+  if ((e = resid_proj(DOWN, ws.down, ws.act, l.wd, a.F, &ws.pending)) != hipSuccess) return e;
   if (l.out) {
     tr.begin(STORE);
     hipLaunchKernelGGL(store_rows_kernel, dim3((unsigned)((TH + 255) / 256)), dim3(256), 0, s, ws.x, ws.part,

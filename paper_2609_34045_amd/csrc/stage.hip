@@ -74,7 +74,6 @@ static int64_t align256(int64_t n) { return (n + 255) & ~(int64_t)255; }
 // device (with that device current) when a stage is created there, and only that
 // address is passed to kernels.  Every no-allocation prefill on a device shares
 // the array, so such calls must not overlap on one device.
-constexpr int64_t kPrefillScratchBytes = 144LL << 20;  // a 512-token chunk of the 70B shape needs 132 MiB
 static __device__ __align__(256) char scratch[kPrefillScratchBytes];
 static_assert(kPrefillScratchBytes == KF_PREFILL_SCRATCH_BYTES, "the header states the scratch size");
 constexpr int kMaxDevices = 64;

@@ -126,3 +126,47 @@ def test_prefill_splitk_tile_widths(torch, st, T):
     print(f"split-K tile widths T={T} prefill max row rel err", err)
     kv.close()
     g.close()
+
+
+@pytest.mark.parametrize("T", [1, 32, 33, 64, 65, 128, 129, 257])
+def test_prefill_row_tiles(torch, st, T):
+    """The projections' row tiles (32, 64, 128 and 256 rows) at their edges, against the float64 oracle.
+
+    Query width 320 and FFN 1088 end in partial column tiles of every width;
+    K = 256, 320 and 1088 give one to four K slices, down to slices of four and
+    five 64-deep steps.
+    """
+    shape = synth.ModelShape(1, 256, 5, 1, 64, 1088, 300, 1e-5, 1e4)
+    cfg = 78
+    model = SeededModel(shape, cfg)
+    g = st.Stage(shape, 0, 1, model.layer, None)
+    kv = g.kv(1, T)
+    h = synth.hidden_states(cfg, synth.STREAM_PREFILL_HIDDEN, 0, T, shape.hidden)
+    y = g.prefill(kv, 0, 0, hidden=torch.from_numpy(h).cuda())
+    o = OracleStage(shape, 0, 1, model.layer, None, max_users=1, max_ctx=T)
+    # what the layer adds to the rows (a few percent of them: a lost block would pass unseen in the sum)
+    err = assert_hidden_close(host(y) - h, o.prefill(0, 0, hidden=h) - h, what=f"prefill T {T}")
+    print(f"row tiles T={T} prefill max row rel err", err)
+    kv.close()
+    g.close()
+
+
+def test_prefill_shorter_chunk_after_longer(torch, st):
+    """A chunk's partial sums may take more room than a longer chunk's (fewer row tiles, more K slices):
+    chunks of 300, 256, 40 and 130 tokens on one stage give the bits that each gives on a stage of its own."""
+    shape = synth.ModelShape(1, 1024, 8, 2, 64, 8192, 300, 1e-5, 1e4)
+    cfg = 79
+    model = SeededModel(shape, cfg)
+    chunks = [300, 256, 40, 130]
+    g = st.Stage(shape, 0, 1, model.layer, None)
+    kv = g.kv(len(chunks), max(chunks))
+    for u, T in enumerate(chunks):
+        h = torch.from_numpy(synth.hidden_states(cfg, synth.STREAM_PREFILL_HIDDEN, u, T, shape.hidden)).cuda()
+        y = g.prefill(kv, u, 0, hidden=h)
+        own = st.Stage(shape, 0, 1, model.layer, None)
+        own_kv = own.kv(1, T)
+        assert torch.equal(y, own.prefill(own_kv, 0, 0, hidden=h)), T
+        own_kv.close()
+        own.close()
+    kv.close()
+    g.close()
