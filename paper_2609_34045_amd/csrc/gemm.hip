@@ -43,6 +43,7 @@ namespace {
 typedef unsigned v4u __attribute__((ext_vector_type(4)));
 typedef _Float16 h8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) void* lds_ptr;
 
 #ifndef KF_GEMM_BK
@@ -108,7 +109,14 @@ struct Params {
   float* C;
   uint16_t* Cb;
   int* err_flag;
+  int rows_out;            // logits: rows of the output (M counts the rows of A)
+  const float* row_scale;  // logits: factor of each output row
 };
+
+// Rows of A per output row: the logits of fp32 rows take each row as two fp16
+// parts, in 32-row blocks of high parts, each followed by the block of the low
+// parts, that add into one accumulator.
+constexpr int parts_of(int epi) { return epi == kGemmLogitsSplit ? 2 : 1; }
 
 constexpr int NW = 8;                        // waves per workgroup
 constexpr int LOADS = TILE_BYTES / 1024 / NW;  // 1 KB direct loads per wave per operand per stage
@@ -144,6 +152,25 @@ __device__ __forceinline__ void store_tile(const Params& p, const f32x16 (&acc)[
         }
       }
     raise_err(p.err_flag, bad, kErrF16Range);
+  } else if (EPI == kGemmLogits || EPI == kGemmLogitsSplit) {
+    bool nan = false;
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const int row = row0 + 32 * i + 8 * (v >> 2) + rq + (v & 3);
+        if (row >= p.rows_out) continue;
+        const float scale = p.row_scale[row];
+#pragma unroll
+        for (int j = 0; j < JW; ++j) {
+          const int col = n0 + 32 * (bw0 + j) + rl;
+          if (col >= p.N) continue;
+          const float y = acc[i][j][v] * scale;
+          nan |= y != y;
+          p.C[(int64_t)row * p.N + col] = y;
+        }
+      }
+    raise_err(p.err_flag, nan, kErrNaNLogit);
   } else {
 #pragma unroll
     for (int i = 0; i < MB; ++i)
@@ -171,6 +198,8 @@ template <int EPI, int MB, int JW, int LW>
 __device__ __forceinline__ void gemm_wave(const Params& p, uint8_t* smem, const uint16_t* const (&asrc)[LOADS],
                                           const uint16_t* const (&wsrc)[LOADS], int nk, int wave, int lane,
                                           int m0, int n0, int am0, int bw0, int ks) {
+  constexpr int PA = parts_of(EPI);  // A blocks per accumulator block
+  static_assert(MB % PA == 0, "whole output blocks");
   constexpr int SLOTS = MB * JW;  // MFMAs per 16-wide K slice
   constexpr int RD = MB + JW;     // fragment reads per slice
   constexpr int LA = LOADS;       // A loads per stage
@@ -190,9 +219,9 @@ __device__ __forceinline__ void gemm_wave(const Params& p, uint8_t* smem, const 
     __builtin_amdgcn_global_load_lds(src, (lds_ptr)dst, 16, 0, 0);
   };
 
-  f32x16 acc[MB][JW];
+  f32x16 acc[MB / PA][JW];
 #pragma unroll
-  for (int i = 0; i < MB; ++i)
+  for (int i = 0; i < MB / PA; ++i)
 #pragma unroll
     for (int j = 0; j < JW; ++j)
 #pragma unroll
@@ -220,7 +249,7 @@ __device__ __forceinline__ void gemm_wave(const Params& p, uint8_t* smem, const 
     constexpr int RPS = KF_GEMM_READS_PER_SLOT;
 #pragma unroll
     for (int q = 0; q < SLOTS; ++q) {
-      acc[q / JW][q % JW] = mfma32(fa[q / JW], fw[q % JW], acc[q / JW][q % JW]);
+      acc[q / JW / PA][q % JW] = mfma32(fa[q / JW], fw[q % JW], acc[q / JW / PA][q % JW]);
 #pragma unroll
       for (int r = 0; r < RPS; ++r)
         if (q * RPS + r < RD) read_frag(rk, rs, q * RPS + r, na, nw);
@@ -277,11 +306,12 @@ __device__ __forceinline__ void gemm_wave(const Params& p, uint8_t* smem, const 
     for (int s = 0; s + 1 < SS; ++s)
       half(fa[s & 1], fw[s & 1], k, s + 1, fa[(s + 1) & 1], fw[(s + 1) & 1], false, 0, 0);
 #pragma unroll
-    for (int q = 0; q < SLOTS; ++q) acc[q / JW][q % JW] = mfma32(fa[1][q / JW], fw[1][q % JW], acc[q / JW][q % JW]);
+    for (int q = 0; q < SLOTS; ++q)
+      acc[q / JW / PA][q % JW] = mfma32(fa[1][q / JW], fw[1][q % JW], acc[q / JW / PA][q % JW]);
   }
   wait_vm<0>();  // no load may still be writing LDS when the workgroup ends
 
-  store_tile<EPI, MB, JW>(p, acc, lane, m0 + am0, n0, bw0, ks);
+  store_tile<EPI, MB / PA, JW>(p, acc, lane, (m0 + am0) / PA, n0, bw0, ks);
 }
 
 // Tiles of 256 rows x 32 NB columns (NB = 8; 7, 5 or 4 where narrower tiles
@@ -306,7 +336,10 @@ __global__ __launch_bounds__(kGemmThreads) void gemm256_kernel(const Params p) {
   // Tiles sharing a weight panel (same column tile) go to the same XCD, where
   // they reuse it through that XCD's L2 (workgroups are dealt round-robin).
   int bid = blockIdx.x;
-  if (nwg % 8 == 0) bid = (bid % 8) * (nwg / 8) + bid / 8;
+  {
+    const int x = bid % 8, q = nwg / 8, r = nwg % 8;  // XCD x holds q workgroups, one more while x < r
+    bid = x * q + (x < r ? x : r) + bid / 8;
+  }
   const int ks = bid % p.splitk, t = bid / p.splitk;
   const int tm = t % mt, tn = t / mt;
   const int m0 = tm * BM, n0 = tn * TN;
@@ -449,9 +482,11 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_rows_kernel(const Params p)
     }
   };
 
-  f32x16 acc[MBW][JW];
+  constexpr int PA = parts_of(EPI);  // A blocks per accumulator block
+  static_assert(MBW % PA == 0, "whole output blocks");
+  f32x16 acc[MBW / PA][JW];
 #pragma unroll
-  for (int i = 0; i < MBW; ++i)
+  for (int i = 0; i < MBW / PA; ++i)
 #pragma unroll
     for (int j = 0; j < JW; ++j)
 #pragma unroll
@@ -493,11 +528,11 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_rows_kernel(const Params p)
 #pragma unroll
       for (int i = 0; i < MBW; ++i)
 #pragma unroll
-        for (int j = 0; j < JW; ++j) acc[i][j] = mfma32(fa[i], fw[j], acc[i][j]);
+        for (int j = 0; j < JW; ++j) acc[i / PA][j] = mfma32(fa[i], fw[j], acc[i / PA][j]);
     }
     wait_lds();  // no read of this step's stage is in flight past the next barrier
   }
-  store_tile<EPI, MBW, JW>(p, acc, lane, m0 + 32 * MBW * wm, n0, JW * wn, ks);
+  store_tile<EPI, MBW / PA, JW>(p, acc, lane, (m0 + 32 * MBW * wm) / PA, n0, JW * wn, ks);
 }
 
 }  // namespace
@@ -531,9 +566,10 @@ GemmPlan gemm_plan(int epi, int M, int N, int K, int64_t part_elems) {
   for (int t = 0; t < (int)(sizeof(kTiles) / sizeof(kTiles[0])); ++t) {
     const Tile& T = kTiles[t];
     if (T.few && M > 128) continue;
+    if (t == 0 && epi == kGemmLogitsSplit) continue;  // its waves hold one 32-row block
     const int64_t tiles = (int64_t)((M + T.rows - 1) / T.rows) * ((N + T.cols - 1) / T.cols);
     for (int s = 1; s <= kGemmMaxSlices && s <= nk / 4; ++s) {
-      if (s > 1 && (epi == kGemmSwiGLU || (int64_t)s * M * N > part_elems)) break;
+      if (s > 1 && (epi != kGemmPartialF32 || (int64_t)s * M * N > part_elems)) break;
       const float us = (float)((tiles * s + 255) / 256) * ((nk + s - 1) / s) * T.step_us + 4.f +
                        (s > 1 ? s : 0) * (float)M * N * 8e-6f / 6.f;
       if (best_us == 0.f || us < best_us) {
@@ -550,7 +586,12 @@ static hipError_t launch_tile(const Params& p, int tile, hipStream_t s) {
   const Tile& T = kTiles[tile];
   const dim3 grid((unsigned)((int64_t)((p.M + T.rows - 1) / T.rows) * ((p.N + T.cols - 1) / T.cols) * p.splitk));
   switch (tile) {
-    case 0: hipLaunchKernelGGL((gemm_rows_kernel<EPI, 1, 1, 1, 4, 4>), grid, dim3(256), 0, s, p); break;
+    case 0:
+      if constexpr (parts_of(EPI) == 1)
+        hipLaunchKernelGGL((gemm_rows_kernel<EPI, 1, 1, 1, 4, 4>), grid, dim3(256), 0, s, p);
+      else
+        return hipErrorInvalidValue;
+      break;
     case 1: hipLaunchKernelGGL((gemm_rows_kernel<EPI, 2, 1, 1, 4, 3>), grid, dim3(256), 0, s, p); break;
     case 2: hipLaunchKernelGGL((gemm_rows_kernel<EPI, 2, 1, 2, 4, 4>), grid, dim3(512), 0, s, p); break;
     case 3: hipLaunchKernelGGL((gemm_rows_kernel<EPI, 2, 2, 2, 4, 3>), grid, dim3(512), 0, s, p); break;
@@ -569,13 +610,111 @@ hipError_t launch_gemm(int epi, const GemmPlan& plan, const uint16_t* A, const u
   if (epi == kGemmSwiGLU && N % 32) return hipErrorInvalidValue;  // whole 16-output gate/up blocks
   // the nonlinearity and the residual update need complete sums: only the partial epilogue splits K
   if (epi != kGemmPartialF32 && plan.slices != 1) return hipErrorInvalidValue;
-  const Params p{A, W, W2, M, N, K, plan.slices, C, Cb, err_flag};
+  const Params p{A, W, W2, M, N, K, plan.slices, C, Cb, err_flag, 0, nullptr};
   switch (epi) {
     case kGemmResidF32: return launch_tile<kGemmResidF32>(p, plan.tile, s);
     case kGemmSwiGLU: return launch_tile<kGemmSwiGLU>(p, plan.tile, s);
     case kGemmPartialF32: return launch_tile<kGemmPartialF32>(p, plan.tile, s);
     default: return hipErrorInvalidValue;
   }
+}
+
+// ------------------------------------------------------------------ logits of many rows
+// The rows of a chunk as matrix operands.  The head's rows are fp32 (or bf16)
+// and stay that exact: each row v (times the gain, where that is not folded
+// into the matrix) is scaled by a power of two that brings its largest value
+// into [2^13, 2^14) and taken as an fp16 high part and the fp16 rounding of
+// what is left, 22 significant bits and never less than 2^-38 of the row's
+// largest value; a bf16 row without a gain is its high part.  The products
+// and their sums are then those of fp32 rows with fp16 weights (error against
+// 64-bit sums, 8B head, 256 rows: 2.0e-4 of the logits before and after, the
+// rounding of the weights).  Row r's factor is 1 / rms(v) and the power of two
+// taken back.  One workgroup per row; rows past `rows` fill their block with zeros.
+template <int PARTS>
+__global__ __launch_bounds__(256) void head_rows_kernel(const void* in, int in_bf16, const uint16_t* gain, int rows,
+                                                        int H, float eps, uint16_t* a, float* row_scale) {
+  const int r = blockIdx.x, tid = threadIdx.x;
+  uint2* hi = reinterpret_cast<uint2*>(a + (int64_t)(PARTS * (r & ~31) + (r & 31)) * H);
+  uint2* lo = reinterpret_cast<uint2*>(a + (int64_t)(PARTS * (r & ~31) + 32 + (r & 31)) * H);
+  if (r >= rows) {
+    for (int k = tid; k < H / 4; k += 256) {
+      hi[k] = uint2{0u, 0u};
+      if (PARTS == 2) lo[k] = uint2{0u, 0u};
+    }
+    return;
+  }
+  auto load = [&](int k) {  // values 4 k .. + 3 before the gain
+    if (in_bf16) {
+      const uint2 e = reinterpret_cast<const uint2*>(in)[(int64_t)r * (H / 4) + k];
+      return f32x4{__uint_as_float(e.x << 16), __uint_as_float(e.x & 0xffff0000u), __uint_as_float(e.y << 16),
+                   __uint_as_float(e.y & 0xffff0000u)};
+    }
+    return reinterpret_cast<const f32x4*>(in)[(int64_t)r * (H / 4) + k];
+  };
+  auto gained = [&](f32x4 v, int k) {
+    if (gain) {
+      const uint2 g = reinterpret_cast<const uint2*>(gain)[k];
+      v *= f32x4{__uint_as_float(g.x << 16), __uint_as_float(g.x & 0xffff0000u), __uint_as_float(g.y << 16),
+                 __uint_as_float(g.y & 0xffff0000u)};
+    }
+    return v;
+  };
+  float ss = 0.f, mx = 0.f;
+  for (int k = tid; k < H / 4; k += 256) {
+    const f32x4 v = load(k), w = gained(v, k);
+    ss += (v.x * v.x + v.y * v.y) + (v.z * v.z + v.w * v.w);
+    mx = fmaxf(fmaxf(mx, fmaxf(fabsf(w.x), fabsf(w.y))), fmaxf(fabsf(w.z), fabsf(w.w)));
+  }
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) {
+    ss += __shfl_xor(ss, o);
+    mx = fmaxf(mx, __shfl_xor(mx, o));
+  }
+  __shared__ float rs[4], rm[4];
+  if ((tid & 63) == 0) {
+    rs[tid >> 6] = ss;
+    rm[tid >> 6] = mx;
+  }
+  __syncthreads();
+  ss = (rs[0] + rs[1]) + (rs[2] + rs[3]);
+  mx = fmaxf(fmaxf(rm[0], rm[1]), fmaxf(rm[2], rm[3]));
+  // a row of zeros or with an infinity keeps its scale (its logits are NaN or
+  // 0 through the factor, as products of the row itself would be)
+  const int e = mx > 0.f && mx < INFINITY ? 13 - ilogbf(mx) : 0;
+  if (tid == 0) row_scale[r] = ldexpf(1.0f / sqrtf(ss / (float)H + eps), -e);
+  for (int k = tid; k < H / 4; k += 256) {
+    const f32x4 w = gained(load(k), k);
+    uint16_t h[4], l[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float v = ldexpf(w[i], e);
+      const _Float16 vh = (_Float16)v;
+      h[i] = __builtin_bit_cast(uint16_t, vh);
+      l[i] = __builtin_bit_cast(uint16_t, (_Float16)(v - (float)vh));
+    }
+    hi[k] = uint2{h[0] | ((uint32_t)h[1] << 16), h[2] | ((uint32_t)h[3] << 16)};
+    if (PARTS == 2) lo[k] = uint2{l[0] | ((uint32_t)l[1] << 16), l[2] | ((uint32_t)l[3] << 16)};
+  }
+}
+
+hipError_t launch_head_logits(const void* in, int in_bf16, const uint16_t* gain, const uint16_t* w, int rows, int N,
+                              int K, float eps, uint16_t* a, float* row_scale, float* logits, int* err_flag,
+                              hipStream_t s) {
+  const int parts = in_bf16 && !gain ? 1 : 2;
+  if (rows <= 0 || rows > kHeadChunk * 2 / parts || N <= 0 || K <= 0 || K % BK) return hipErrorInvalidValue;
+  const int blocks = (rows + 31) / 32, epi = parts == 1 ? kGemmLogits : kGemmLogitsSplit;
+  if (parts == 1)
+    hipLaunchKernelGGL(head_rows_kernel<1>, dim3(32 * blocks), dim3(256), 0, s, in, in_bf16, gain, rows, K, eps, a,
+                       row_scale);
+  else
+    hipLaunchKernelGGL(head_rows_kernel<2>, dim3(32 * blocks), dim3(256), 0, s, in, in_bf16, gain, rows, K, eps, a,
+                       row_scale);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  const int M = 32 * blocks * parts;
+  const Params p{a, w, nullptr, M, N, K, 1, logits, nullptr, err_flag, rows, row_scale};
+  const int tile = gemm_plan(epi, M, N, K, 0).tile;
+  return parts == 1 ? launch_tile<kGemmLogits>(p, tile, s) : launch_tile<kGemmLogitsSplit>(p, tile, s);
 }
 
 }  // namespace kf

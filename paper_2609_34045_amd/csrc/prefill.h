@@ -35,7 +35,9 @@ struct PrefillLayer {
 //   kGemmSwiGLU     Cb[M][N/2] = silu(gate) * up in fp16, W the gate rows and W2 the up rows
 //   kGemmPartialF32 K slice ks to C + ks*M*N (plain stores); the consumer adds the
 //                   plan's slices in order
-enum GemmEpi : int { kGemmResidF32 = 1, kGemmSwiGLU = 2, kGemmPartialF32 = 3 };
+//   kGemmLogits     C[r][N] = row_scale[r] A W^T; kGemmLogitsSplit: with each row of A in two
+//                   parts (launch_head_logits)
+enum GemmEpi : int { kGemmResidF32 = 1, kGemmSwiGLU = 2, kGemmPartialF32 = 3, kGemmLogits = 4, kGemmLogitsSplit = 5 };
 constexpr int kGemmMaxSlices = 8;  // K slices that the consuming kernels add
 // Tile shape and K slices of one product.  `part_elems`: fp32 values that the slices may take.
 struct GemmPlan {
@@ -44,6 +46,14 @@ struct GemmPlan {
 GemmPlan gemm_plan(int epi, int M, int N, int K, int64_t part_elems);
 hipError_t launch_gemm(int epi, const GemmPlan& plan, const uint16_t* A, const uint16_t* W, const uint16_t* W2, int M,
                        int N, int K, float* C, uint16_t* Cb, int* err_flag, hipStream_t s);
+
+// Logits of many rows: logits[rows][N] = RMSNorm(in; gain) W^T on the matrix cores, for
+// up to kHeadChunk fp32 rows (2 kHeadChunk bf16 rows when gain is NULL, i.e. folded into W).
+// a: [2 kHeadChunk][K] fp16 and row_scale: [2 kHeadChunk] are workspace.
+constexpr int kHeadChunk = 256;  // 128 rows a chunk read the matrix twice as often: 256 rows 582 us against 521 (8B)
+hipError_t launch_head_logits(const void* in, int in_bf16, const uint16_t* gain, const uint16_t* w, int rows, int N,
+                              int K, float eps, uint16_t* a, float* row_scale, float* logits, int* err_flag,
+                              hipStream_t s);
 
 // Device workspace, grown on demand to the largest chunk seen and laid out anew for each chunk.
 struct PrefillWorkspace {

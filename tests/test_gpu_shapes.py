@@ -170,3 +170,56 @@ def test_prefill_shorter_chunk_after_longer(torch, st):
         own.close()
     kv.close()
     g.close()
+
+
+@pytest.mark.parametrize("fold", [True, False], ids=["gain_folded", "gain_apart"])
+@pytest.mark.parametrize("io", ["float32", "bfloat16"])
+@pytest.mark.parametrize("rows", [5, 33, 64, 129, 300])
+def test_logits_of_many_rows(torch, st, rows, io, fold):
+    """More rows than one GEMV pass takes (the matrix-core logits), at the edges of their tiles and chunks.
+
+    Rows of very different scales (1e-30 to 1e15, and values 1e-6 of their row's
+    largest), one of zeros, one with an infinity and one with a NaN, over a
+    vocabulary that ends in a partial tile.  Against the GEMV on the same rows, four at a
+    time: both take fp32 sums of the same exact products, so they differ by the
+    order of the sums alone, at most 2 K 2^-24 of sum |w x| (K = 320), which
+    for these random rows is under 10 times the largest logit: 4e-4; and the
+    rows' relative error against float64 (their matrix as stored, fp16 with the gain) stays
+    under 1e-3.
+    """
+    shape = synth.ModelShape(1, 320, 5, 1, 64, 64, 777, 1e-5, 1e4)
+    cfg = 80
+    model = SeededModel(shape, cfg)
+    head = dict(model.head())
+    if not fold:  # one product beyond fp16 keeps the gain out of the matrix
+        gain = np.array(head["final_norm"], copy=True)
+        gain[7] = 0x4974  # 1e6 in bf16
+        head["final_norm"] = gain
+    g = st.Stage(shape, 0, 1, model.layer, head)
+    o = OracleStage(shape, 0, 1, model.layer, head, max_users=1, max_ctx=1)
+    x = synth.hidden_states(cfg, synth.STREAM_DECODE_HIDDEN, 0, rows, shape.hidden)
+    x[0, ::3] *= 1e-6
+    x[1] *= 1e15
+    x[2] *= 1e-30
+    x[3] = 0
+    x = torch.from_numpy(x).to(getattr(torch, io)).cuda()
+    whole = g.head_logits(x)
+    g.sync()
+    parts = torch.cat([g.head_logits(x[r:r + 4].contiguous()) for r in range(0, rows, 4)])
+    ref = o.logits(x.double().cpu().numpy())
+    got, want = host(whole), host(parts)
+    keep = np.array([r for r in range(rows) if r != 3])
+    scale = np.max(np.abs(want[keep]), axis=1, keepdims=True)
+    assert np.all(np.isfinite(got))
+    assert np.max(np.abs(got[keep] - want[keep]) / scale) <= 4e-4
+    assert np.max(np.abs(got[keep] - ref[keep]) / np.max(np.abs(ref[keep]), axis=1, keepdims=True)) <= 1e-3
+    assert not got[3].any()
+    x[0, 5] = float("inf")
+    x[rows - 1, 9] = float("nan")
+    bad = g.head_logits(x)
+    with pytest.raises(st.KFError) as e:
+        g.sync()
+    assert e.value.status == st.KF_ERANGE
+    assert torch.isnan(bad[0]).all() and torch.isnan(bad[rows - 1]).all()
+    assert torch.equal(bad[1:rows - 1], whole[1:rows - 1])
+    g.close()
