@@ -64,6 +64,7 @@ struct PrefillWorkspace {
   float* part = nullptr;   // split-K partial sums [slices][T][N] of the last split projection, or attention partials
   int64_t part_elems = 0;  // values at part
   GemmPlan qkv, oproj, gateup, down;  // the chunk's projections
+  int attn_z = 1;                     // key splits of its attention
   int pending = 0;         // slices of the down projection in `part` not yet added to x
   uint16_t* q = nullptr;   // [T][nq][hd] rotated queries, fp16
   uint16_t* o = nullptr;   // [T][nq hd] attention output, fp16

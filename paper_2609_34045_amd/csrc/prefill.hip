@@ -64,9 +64,6 @@ __device__ __forceinline__ f32x16 mfma32(v4u a, v4u b, f32x16 c) {
 // row loops are unrolled by 4, so the loads of four 16-byte steps are in flight
 // together (70B-shaped rows: 24.6 -> 21.1 us per norm).
 constexpr int kMaxSlices = kGemmMaxSlices;
-#ifndef KF_PF_ATTN_SPLIT
-#define KF_PF_ATTN_SPLIT 2  // key splits of the prefill attention when the chunk gives < 512 workgroups
-#endif
 
 __global__ __launch_bounds__(256) void rmsnorm_rows_f16_kernel(float* __restrict__ x, const float* __restrict__ part, int nsplit,
                                                                 int64_t stride, const uint16_t* __restrict__ g, float eps,
@@ -176,7 +173,11 @@ __global__ __launch_bounds__(256) void rope_kv_kernel(const float* qkv, int nspl
 }
 
 // ------------------------------------------------------------------ causal flash attention
-// Workgroup = (128 queries, one query head); wave w owns queries 32w .. 32w+31.
+// Workgroup = (128 query rows, one KV head).  The rows of a KV head are the
+// chunk's tokens times the G query heads of its group, token by token, so a
+// tile of 128 rows holds 128 / G tokens: short chunks fill their tiles (64
+// tokens of a G = 4 shape are 2 full tiles per KV head, where a tile per query head
+// is half empty) and fewer keys are masked.  Wave w owns rows 32w .. 32w+31.
 // Per block of 64 keys each wave computes S^T = K Q^T (keys x queries) so that
 // every lane holds one query's column; the online softmax is then per lane, and
 // the lane's probabilities are already a B fragment of O^T += V^T P^T once the
@@ -191,10 +192,10 @@ __global__ __launch_bounds__(256) void rope_kv_kernel(const float* qkv, int nspl
 // the softmax of block j.  K and V have 2-stage rings of their own, each
 // loaded one iteration ahead, right after the barrier that frees its stage.
 //
-// The keys may be split over gridDim.z workgroups (more workgroups in flight,
-// two per CU): split z takes key blocks [z nblk / Z, (z+1) nblk / Z) and, when
-// Z > 1, writes its unnormalised output and (max, sum) per query to part_acc /
-// part_ml for attn_prefill_combine_kernel.
+// The keys may be split over gridDim.z workgroups (attn_splits: more workgroups
+// in flight, two per CU): split z takes key blocks [z nblk / Z, (z+1) nblk / Z)
+// and, when Z > 1, writes its unnormalised output and (max, sum) per query to
+// part_acc / part_ml for attn_prefill_combine_kernel.
 #ifndef KF_PF_ATTN_RING
 #define KF_PF_ATTN_RING 4
 #endif
@@ -269,14 +270,17 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(const uint16_t* q,
       bx = (l / gridDim.z) % nx;
       by = l / (gridDim.z * nx);
     }
+    bx = nx - 1 - bx;  // the tiles that see the most keys start first
   }
-  const int h = by, g = h / (nq / nkv);
-  const int i0 = bx * 128;
-  const int qi = i0 + wave * 32 + (lane & 31);  // this lane's query (chunk index)
+  const int g = by, G = nq / nkv, rows = T * G;
+  const int r0 = bx * 128 + wave * 32;          // the wave's first row
+  const int row = r0 + (lane & 31);             // this lane's row of the KV head
   const int half_sel = lane >> 5;
-  const bool qok = qi < T;
+  const bool qok = row < rows;
+  const bool live = r0 < rows;                  // a wave without rows only loads
+  const int qi = min(row, rows - 1) / G, h = g * G + min(row, rows - 1) % G;  // token (chunk index) and query head
   const int qpos = pos0 + qi;
-  const int last_q = min(i0 + 127, T - 1);
+  const int last_q = min(bx * 128 + 127, rows - 1) / G;
   const int nkeys = pos0 + last_q + 1;  // keys visible to the workgroup's last query
   const int nblk_all = (nkeys + KB - 1) / KB;
   const int Z = gridDim.z, z = bz;
@@ -300,7 +304,7 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(const uint16_t* q,
   // Q^T fragments: lane holds query qi, d = 16 s + 8 half_sel .. +7.
   v4u qf[NS];
   {
-    const uint16_t* qr = q + ((int64_t)(qok ? qi : 0) * nq + h) * HD;
+    const uint16_t* qr = q + ((int64_t)qi * nq + h) * HD;
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
       v4u v = *reinterpret_cast<const v4u*>(qr + 16 * s + 8 * half_sel);
@@ -564,7 +568,8 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(const uint16_t* q,
     }
     if (blk + 2 < blk1) issue(kc, blk + 2, k_this);
     if (blk + 1 < blk1) issue(vc, blk + 1, v_next);
-    if (blk * KB + KB - 1 > pos0 + i0 + wave * 32) mask(blk, sc);
+    if (!live) return;
+    if (blk * KB + KB - 1 > pos0 + r0 / G) mask(blk, sc);
     v4u pf[NT][2];
     float alpha;
     if (blk + 1 < blk1) alpha = s_mfma_softmax(k_next, sn, sc, pf);
@@ -585,7 +590,7 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(const uint16_t* q,
     attn_wait_loads();
     attn_barrier();
     if (blk0 + 1 < blk1) issue(kc, blk0 + 1, kst(blk0 + 1));
-    s_mfma(kst(blk0), sa);
+    if (live) s_mfma(kst(blk0), sa);
   }
   int blk = blk0;
   for (; blk + 1 < blk1; blk += 2) {
@@ -624,47 +629,42 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(const uint16_t* q,
 }
 
 // Merge of Z key splits: o[q][h][d] = sum_z 2^(m_z - M) acc_z[d] / sum_z 2^(m_z - M) l_z
-// (a split without keys has m = -inf, l = 0 and weight 0).  One thread per 4 dims;
-// the (max, sum) pairs and vectors of the first four splits are requested together,
-// so the merge takes one memory round trip (70B-shaped attention with its merge
-// 97.0 -> 93.5 us per layer).
-template <int HD>
+// (a split without keys has m = -inf, l = 0 and weight 0).  One thread per 4 dims; the
+// (max, sum) pairs and vectors of ZP splits are requested together, so up to ZP
+// splits take one memory round trip (70B-shaped attention with its merge of two
+// 97.0 -> 93.5 us per layer); further ones are merged into the running maximum.
+template <int HD, int ZP>
 __global__ __launch_bounds__(256) void attn_prefill_combine_kernel(const float* part_acc, const float* part_ml,
                                                                    uint16_t* out, int rows, int Z, int* err_flag) {
   const int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;  // over rows * HD/4
   if (e >= (int64_t)rows * (HD / 4)) return;
   const int64_t r = e / (HD / 4);
   const int d4 = (int)(e % (HD / 4));
-  constexpr int ZP = 4;  // splits whose (max, sum) and vector are requested together
-  float2 mlp[ZP];
-  v4f ap[ZP];
-#pragma unroll
-  for (int z = 0; z < ZP; ++z) {
-    const int zz = z < Z ? z : 0;
-    mlp[z] = reinterpret_cast<const float2*>(part_ml)[(int64_t)zz * rows + r];
-    ap[z] = reinterpret_cast<const v4f*>(part_acc + ((int64_t)zz * rows + r) * HD)[d4];
-  }
-  float M = -INFINITY;
-#pragma unroll
-  for (int z = 0; z < ZP; ++z)
-    if (z < Z && mlp[z].y > 0.f) M = fmaxf(M, mlp[z].x);
-  for (int z = ZP; z < Z; ++z) {
-    const float m = part_ml[((int64_t)z * rows + r) * 2], l = part_ml[((int64_t)z * rows + r) * 2 + 1];
-    if (l > 0.f) M = fmaxf(M, m);
-  }
   v4f acc = {0.f, 0.f, 0.f, 0.f};
-  float L = 0.f;
+  float M = -INFINITY, L = 0.f;
+  for (int z0 = 0; z0 < Z; z0 += ZP) {
+    float2 ml[ZP];
+    v4f ap[ZP];
 #pragma unroll
-  for (int z = 0; z < ZP; ++z) {
-    const float w = z < Z && mlp[z].y > 0.f ? exp2f(mlp[z].x - M) : 0.f;
-    acc += w * ap[z];
-    L += w * mlp[z].y;
-  }
-  for (int z = ZP; z < Z; ++z) {
-    const float m = part_ml[((int64_t)z * rows + r) * 2], l = part_ml[((int64_t)z * rows + r) * 2 + 1];
-    const float w = l > 0.f ? exp2f(m - M) : 0.f;
-    acc += w * reinterpret_cast<const v4f*>(part_acc + ((int64_t)z * rows + r) * HD)[d4];
-    L += w * l;
+    for (int i = 0; i < ZP; ++i) {
+      const int z = min(z0 + i, Z - 1);
+      ml[i] = reinterpret_cast<const float2*>(part_ml)[(int64_t)z * rows + r];
+      ap[i] = reinterpret_cast<const v4f*>(part_acc + ((int64_t)z * rows + r) * HD)[d4];
+    }
+    float m = M;
+#pragma unroll
+    for (int i = 0; i < ZP; ++i)
+      if (z0 + i < Z && ml[i].y > 0.f) m = fmaxf(m, ml[i].x);
+    const float f = L > 0.f ? exp2f(M - m) : 0.f;
+    M = m;
+    acc *= f;
+    L *= f;
+#pragma unroll
+    for (int i = 0; i < ZP; ++i) {
+      const float w = z0 + i < Z && ml[i].y > 0.f ? exp2f(ml[i].x - M) : 0.f;
+      acc += w * ap[i];
+      L += w * ml[i].y;
+    }
   }
   acc *= 1.0f / L;
   bool bad = false;
@@ -756,6 +756,29 @@ static int64_t part_bytes(const PrefillArgs& a) {
   return std::max(sized, std::min(kPartSmall, kPrefillScratchBytes - other));
 }
 
+// Key splits of the attention of least estimated time: the blocks of a split
+// (1.7 us each with one workgroup on a CU, 2.6 us with two), the partial
+// results written and read (5 TB/s) and the launch that merges them, over the
+// workgroups' rounds of two per CU.
+static int attn_splits(const PrefillArgs& a, int64_t part_elems) {
+  const int64_t tiles = ((int64_t)a.T * (a.nq / a.nkv) + 127) / 128 * a.nkv;
+  const int nblk = (a.pos0 + a.T + kAttnKB - 1) / kAttnKB;
+  const int64_t elems = (int64_t)a.T * a.nq * (a.hd + 2);  // partials of one split
+  int best = 1;
+  float best_us = 0.f;
+  for (int z = 1; z <= 64 && z <= (nblk + 1) / 2; ++z) {
+    if (z > 1 && z * elems > part_elems) break;
+    const int64_t wgs = tiles * z, rest = wgs % 512;
+    const float rounds = (float)(wgs / 512) * 2.6f + (rest == 0 ? 0.f : rest <= 256 ? 1.7f : 2.6f);
+    const float us = rounds * (float)((nblk + z - 1) / z) + (z > 1 ? 5.f + (float)(z * elems) * 8.f / 5e6f : 0.f);
+    if (z == 1 || us < best_us) {
+      best = z;
+      best_us = us;
+    }
+  }
+  return best;
+}
+
 void prefill_carve(PrefillWorkspace& ws, char* base, const PrefillArgs& a) {
   int64_t sz[5];
   other_sizes(a, sz);
@@ -776,6 +799,7 @@ void prefill_carve(PrefillWorkspace& ws, char* base, const PrefillArgs& a) {
   ws.qkv = gemm_plan(kGemmPartialF32, a.T, (a.nq + 2 * a.nkv) * a.hd, a.H, ws.part_elems);
   ws.oproj = gemm_plan(kGemmPartialF32, a.T, a.H, a.nq * a.hd, ws.part_elems);
   ws.gateup = gemm_plan(kGemmSwiGLU, a.T, 2 * a.F, a.H, 0);
+  ws.attn_z = attn_splits(a, ws.part_elems);
   ws.down = gemm_plan(kGemmPartialF32, a.T, a.H, a.F, ws.part_elems);
 }
 
@@ -831,10 +855,8 @@ hipError_t prefill_layer(PrefillWorkspace& ws, const PrefillArgs& a, const Prefi
   tr.end(ROPE);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   const float sl2 = (float)(1.4426950408889634 / std::sqrt((double)a.hd));
-  // Key splits: enough workgroups for two per CU when the chunk alone gives fewer.
-  const int qtiles = (T + 127) / 128;
-  const int Z = qtiles * a.nq >= 512 ? 1 : KF_PF_ATTN_SPLIT;
-  const dim3 ag(qtiles, a.nq, Z);
+  const int Z = ws.attn_z;
+  const dim3 ag((unsigned)(((int64_t)T * (a.nq / a.nkv) + 127) / 128), a.nkv, Z);
   float* pacc = ws.part;
   float* pml = ws.part + (int64_t)Z * T * a.nq * a.hd;
   tr.begin(ATTN);
@@ -851,10 +873,14 @@ hipError_t prefill_layer(PrefillWorkspace& ws, const PrefillArgs& a, const Prefi
     const int rows = T * a.nq;
     const int64_t n = (int64_t)rows * (a.hd / 4);
     const dim3 cg((unsigned)((n + 255) / 256));
-    if (a.hd == 128)
-      hipLaunchKernelGGL(attn_prefill_combine_kernel<128>, cg, dim3(256), 0, s, pacc, pml, ws.o, rows, Z, a.err_flag);
+    if (a.hd == 128 && Z <= 4)
+      hipLaunchKernelGGL((attn_prefill_combine_kernel<128, 4>), cg, dim3(256), 0, s, pacc, pml, ws.o, rows, Z, a.err_flag);
+    else if (a.hd == 128)
+      hipLaunchKernelGGL((attn_prefill_combine_kernel<128, 16>), cg, dim3(256), 0, s, pacc, pml, ws.o, rows, Z, a.err_flag);
+    else if (Z <= 4)
+      hipLaunchKernelGGL((attn_prefill_combine_kernel<64, 4>), cg, dim3(256), 0, s, pacc, pml, ws.o, rows, Z, a.err_flag);
     else
-      hipLaunchKernelGGL(attn_prefill_combine_kernel<64>, cg, dim3(256), 0, s, pacc, pml, ws.o, rows, Z, a.err_flag);
+      hipLaunchKernelGGL((attn_prefill_combine_kernel<64, 16>), cg, dim3(256), 0, s, pacc, pml, ws.o, rows, Z, a.err_flag);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   tr.end(ATTN);

@@ -223,3 +223,30 @@ def test_logits_of_many_rows(torch, st, rows, io, fold):
     assert torch.isnan(bad[0]).all() and torch.isnan(bad[rows - 1]).all()
     assert torch.equal(bad[1:rows - 1], whole[1:rows - 1])
     g.close()
+
+
+@pytest.mark.parametrize("nq,nkv,hd,T", [(6, 2, 64, 1), (6, 2, 64, 45), (5, 1, 128, 20), (8, 1, 64, 130), (4, 4, 128, 129)],
+                         ids=["g3_t1", "g3_t45", "g5_t20", "g8_t130", "g1_t129"])
+def test_prefill_short_chunk_over_long_cache(torch, st, nq, nkv, hd, T):
+    """Short chunks over 3000 cached keys: the attention's keys go to up to 23 workgroups per tile of 128 rows
+    (tokens x query heads of a KV head), past the 16 splits merged in one pass, with tiles that end inside a
+    token (G = 3, 5), in rows without a token, and waves without rows.  Values of unit variance, so that the
+    attention carries what the layer adds; compared with the float64 oracle's addition."""
+    shape = synth.ModelShape(1, 256, nq, nkv, hd, 64, 300, 1e-5, 1e4)
+    cfg, n0 = 81 + nq, 3000
+    model = SeededModel(shape, cfg)
+    k, v = synth.injected_kv(shape, cfg, 0, 0, n0)
+    v[7::211] = (0x40C0, )  # some values of 6: each split's share of the weights shows
+    h = synth.hidden_states(cfg, synth.STREAM_PREFILL_HIDDEN, 0, T, shape.hidden)
+    o = OracleStage(shape, 0, 1, model.layer, None, max_users=1, max_ctx=n0 + T)
+    o.kv.inject(0, 0, 0, k, v)
+    o.kv.set_len(0, n0)
+    g = st.Stage(shape, 0, 1, model.layer, None)
+    kv = g.kv(1, n0 + T)
+    kv.write(0, 0, 0, torch.from_numpy(k.view(np.int16)).cuda(), torch.from_numpy(v.view(np.int16)).cuda())
+    kv.set_len(0, n0)
+    y = g.prefill(kv, 0, n0, hidden=torch.from_numpy(h).cuda())
+    err = assert_hidden_close(host(y) - h, o.prefill(0, n0, hidden=h) - h, what=f"short chunk T {T}")
+    print(f"G={nq // nkv} hd={hd} T={T} over {n0} keys: max row rel err of the addition", err)
+    kv.close()
+    g.close()
