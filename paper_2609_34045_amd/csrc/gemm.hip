@@ -46,41 +46,20 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) void* lds_ptr;
 
-#ifndef KF_GEMM_BK
-#define KF_GEMM_BK 64
-#endif
-constexpr int BM = 256, BN = 256, BK = KF_GEMM_BK;
-static_assert(BK == 32 || BK == 64, "K step");
-constexpr int kGemmThreads = 512;  // eight waves, two per SIMD
-#ifndef KF_GEMM_READS_PER_SLOT
-#define KF_GEMM_READS_PER_SLOT 1  // fragment reads issued per MFMA slot
-#endif
-#ifndef KF_GEMM_STAGES
-#define KF_GEMM_STAGES (BK == 32 ? 4 : 2)
-#endif
-#ifndef KF_GEMM_WSTAGES
-#define KF_GEMM_WSTAGES (BK == 32 ? 4 : 3)
-#endif
-// LDS ring depths: activation loads run up to SA K steps ahead, weight loads up to SW.
-constexpr int SA = KF_GEMM_STAGES, SW = KF_GEMM_WSTAGES;
-constexpr int TILE_BYTES = BM * BK * 2;     // one operand's tile per stage (16 or 32 KB)
-constexpr int ROW_BYTES = BK * 2;           // 64 or 128 B per tile row
-constexpr int CH = BK / 8;                  // 16-byte chunks per tile row
-constexpr int SS = BK / 16;                 // 16-wide K slices (MFMA steps) per K step
-static_assert(SA >= 2 && SW >= SA && SW <= SA + 1 && (SA + SW) * TILE_BYTES <= 160 * 1024, "ring depths");
+constexpr int BK = 64;             // K step
+constexpr int ROW_BYTES = BK * 2;  // bytes per tile row and step: a cache line
+constexpr int CH = BK / 8;         // 16-byte chunks per tile row
+constexpr int SS = BK / 16;        // 16-wide K slices (MFMA steps) per K step
 
 __device__ __forceinline__ f32x16 mfma32(v4u a, v4u b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(h8, a), __builtin_bit_cast(h8, b), c, 0, 0, 0);
 }
 
-// Chunk c of tile row r is stored at slot c ^ f(r) of that row.  Four chunks
-// per row: f(r) = (r/2 ^ r/4) % 4; eight: f(r) = r % 8 ^ (r/8) % 2.  Either way
-// any 8 consecutive rows hit distinct 16-byte bank groups of a 32-bank LDS,
-// and any 16 consecutive rows of a 64-bank one, so the fragment reads (one
-// row per lane) are free of bank conflicts.
-__device__ __forceinline__ int swz(int r, int c) {
-  return CH == 4 ? c ^ (((r >> 1) ^ (r >> 2)) & 3) : c ^ ((r & 7) ^ ((r >> 3) & 1));
-}
+// Chunk c of tile row r is stored at slot c ^ f(r) of that row, f(r) = r % 8 ^
+// (r/8) % 2: any 8 consecutive rows hit distinct 16-byte bank groups of a
+// 32-bank LDS, and any 16 consecutive rows of a 64-bank one, so the fragment
+// reads (one row per lane) are free of bank conflicts.
+__device__ __forceinline__ int swz(int r, int c) { return c ^ ((r & 7) ^ ((r >> 3) & 1)); }
 
 // Wait until at most N vector-memory operations of this wave are outstanding.
 template <int N>
@@ -118,8 +97,16 @@ struct Params {
 // parts, that add into one accumulator.
 constexpr int parts_of(int epi) { return epi == kGemmLogitsSplit ? 2 : 1; }
 
-constexpr int NW = 8;                        // waves per workgroup
-constexpr int LOADS = TILE_BYTES / 1024 / NW;  // 1 KB direct loads per wave per operand per stage
+// Large tiles: TM rows (256 or 128) x 32 NB columns, eight waves (two per SIMD).
+// LDS ring depths: activation loads run up to ring_a K steps ahead, weight
+// loads up to ring_w; as deep as 160 KB allow (with the depths of the widest, 2
+// and 3, tiles of 128 columns waited on their activations: 8B-shaped gate/up
+// at 200 rows 77.0 -> 69.2 us).
+constexpr int NW = 8;
+constexpr int ring_a(int TM, int NB) { return TM == 256 && NB >= 7 ? 2 : 3; }
+constexpr int ring_w(int NB) { return NB == 4 ? 4 : 3; }
+constexpr int a_stage(int TM) { return TM * ROW_BYTES; }
+constexpr int w_stage(int NB) { return 32 * NB * ROW_BYTES; }
 
 // Epilogue of one wave's accumulators: MB 32-row blocks from output row row0
 // times JW 32-column blocks from block bw0 of the tile at column n0.  Lane l
@@ -192,24 +179,25 @@ __device__ __forceinline__ void store_tile(const Params& p, const f32x16 (&acc)[
 
 // One wave's share of a tile: the K loop and the epilogue for MB 32-row A
 // blocks from tile row am0 times JW 32-column W blocks from block bw0.  Every
-// wave also issues its share of the tile loads: LOADS of the A tile and LW of
-// the W tile per stage (LW < LOADS leaves W tile rows past the tile unloaded).
-template <int EPI, int MB, int JW, int LW>
-__device__ __forceinline__ void gemm_wave(const Params& p, uint8_t* smem, const uint16_t* const (&asrc)[LOADS],
-                                          const uint16_t* const (&wsrc)[LOADS], int nk, int wave, int lane,
+// wave also issues its share of the tile loads: TM / 64 of the A tile and LW of
+// the W tile per stage.
+template <int EPI, int TM, int NB, int MB, int JW, int LW>
+__device__ __forceinline__ void gemm_wave(const Params& p, uint8_t* smem, const uint16_t* const (&asrc)[TM / 64],
+                                          const uint16_t* const (&wsrc)[4], int nk, int wave, int lane,
                                           int m0, int n0, int am0, int bw0, int ks) {
+  constexpr int SA = ring_a(TM, NB), SW = ring_w(NB);
   constexpr int PA = parts_of(EPI);  // A blocks per accumulator block
   static_assert(MB % PA == 0, "whole output blocks");
   constexpr int SLOTS = MB * JW;  // MFMAs per 16-wide K slice
   constexpr int RD = MB + JW;     // fragment reads per slice
-  constexpr int LA = LOADS;       // A loads per stage
+  constexpr int LA = TM / 64;     // A loads per stage
   constexpr int NL = LA + LW;     // direct loads per slice that carries them
-  static_assert(RD <= SLOTS && LW <= LOADS, "a slice's slots issue its reads");
+  static_assert(RD <= SLOTS && LW <= 4, "a slice's slots issue its reads");
 
   // Step kt's stages; past the last step a load fetches step nk-1 again (into
   // the stage of the step it stands in for, which is never read).
-  auto abuf = [&](int kt) { return smem + (kt % SA) * TILE_BYTES; };
-  auto wbuf = [&](int kt) { return smem + (SA + kt % SW) * TILE_BYTES; };
+  auto abuf = [&](int kt) { return smem + (kt % SA) * a_stage(TM); };
+  auto wbuf = [&](int kt) { return smem + SA * a_stage(TM) + (kt % SW) * w_stage(NB); };
   auto src_step = [&](int kt) { return (int64_t)(kt < nk ? kt : nk - 1) * BK; };
   // (named operands: the host pass drops the kernel's launch stub when the
   // builtin's pointer argument is a call expression)
@@ -242,17 +230,14 @@ __device__ __forceinline__ void gemm_wave(const Params& p, uint8_t* smem, const 
     else fa[q - JW] = v;
   };
   // One slice: the SLOTS MFMAs on (fa, fw), the reads of the next fragments
-  // (slice rs of step rk) into (na, nw), RPS per slot from slot 0, and
+  // (slice rs of step rk) into (na, nw), one per slot from slot 0, and
   // optionally the loads of steps ka (A, issued first) and kw (W).
   auto half = [&](const v4u (&fa)[MB], const v4u (&fw)[JW], int rk, int rs, v4u (&na)[MB], v4u (&nw)[JW],
                   bool load, int ka, int kw) {
-    constexpr int RPS = KF_GEMM_READS_PER_SLOT;
 #pragma unroll
     for (int q = 0; q < SLOTS; ++q) {
       acc[q / JW / PA][q % JW] = mfma32(fa[q / JW], fw[q % JW], acc[q / JW / PA][q % JW]);
-#pragma unroll
-      for (int r = 0; r < RPS; ++r)
-        if (q * RPS + r < RD) read_frag(rk, rs, q * RPS + r, na, nw);
+      if (q < RD) read_frag(rk, rs, q, na, nw);
       if (load) {
 #pragma unroll
         for (int l = q * NL / SLOTS; l < (q + 1) * NL / SLOTS; ++l) load_one(l >= LA, l >= LA ? l - LA : l, l >= LA ? kw : ka);
@@ -314,24 +299,25 @@ __device__ __forceinline__ void gemm_wave(const Params& p, uint8_t* smem, const 
   store_tile<EPI, MB / PA, JW>(p, acc, lane, (m0 + am0) / PA, n0, bw0, ks);
 }
 
-// Tiles of 256 rows x 32 NB columns (NB = 8; 7, 5 or 4 where narrower tiles
-// fill the chip in less time: see gemm_plan).  With NB = 8 the
-// eight waves are 2 x 4 of 128 x 64; with NB = 7 (5) they are 4 x 2 of 64 x 128
-// (96) and 64 x 96 (64), so that with waves dealt to the SIMDs round-robin each
-// SIMD holds one of each; with NB = 4, 4 x 2 of 64 x 64.  The W tile is loaded
-// as 256 rows for NB = 8 and 7 (rows past 32 NB repeat the tile's last row and
-// are not used); for NB = 5 and 4 only the loads that hold the tile's rows are
-// issued.
-template <int EPI, int NB>
-__global__ __launch_bounds__(kGemmThreads) void gemm256_kernel(const Params p) {
-  static_assert(NB == 8 || NB == 7 || NB == 5 || NB == 4, "tile widths");
-  // SA A tiles, then SW W tiles, each [256 rows][CH swizzled 16-byte chunks]; both fp16.
-  __shared__ __attribute__((aligned(1024))) uint8_t smem[(SA + SW) * TILE_BYTES];
+// Tiles of TM rows x 32 NB columns (narrower or lower ones where they fill the
+// chip in less time: see gemm_plan).  At 256 rows: with NB = 8 the eight waves
+// are 2 x 4 of 128 x 64; with NB = 7 (5) they are 4 x 2 of 64 x 128 (96) and 64
+// x 96 (64), so that with waves dealt to the SIMDs round-robin each SIMD holds
+// one of each; with NB = 4, 4 x 2 of 64 x 64.  The 128-row tile (2 x 4 waves of
+// 64 x 64) serves chunks that end in less than half a 256-row tile (300 rows:
+// 70B-shaped gate/up 431 -> 402 us, 32B-shaped down 133 -> 118).
+template <int EPI, int TM, int NB>
+__global__ __launch_bounds__(64 * NW) void gemm_tile_kernel(const Params p) {
+  static_assert(TM == 256 ? NB == 8 || NB == 7 || NB == 5 || NB == 4 : TM == 128 && NB == 8, "tiles");
+  constexpr int SA = ring_a(TM, NB), SW = ring_w(NB), LDS = SA * a_stage(TM) + SW * w_stage(NB);
+  static_assert(SA >= 2 && SW >= SA && SW <= SA + 1 && LDS <= 160 * 1024, "ring depths");
+  // SA A stages, then SW W stages, of rows of CH swizzled 16-byte chunks; both fp16.
+  __shared__ __attribute__((aligned(1024))) uint8_t smem[LDS];
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   constexpr int TN = 32 * NB;  // tile columns
-  const int mt = (p.M + BM - 1) / BM, nt = (p.N + TN - 1) / TN, ntiles = mt * nt;
+  const int mt = (p.M + TM - 1) / TM, nt = (p.N + TN - 1) / TN, ntiles = mt * nt;
   const int nwg = ntiles * p.splitk;
   // Tiles sharing a weight panel (same column tile) go to the same XCD, where
   // they reuse it through that XCD's L2 (workgroups are dealt round-robin).
@@ -342,62 +328,53 @@ __global__ __launch_bounds__(kGemmThreads) void gemm256_kernel(const Params p) {
   }
   const int ks = bid % p.splitk, t = bid / p.splitk;
   const int tm = t % mt, tn = t / mt;
-  const int m0 = tm * BM, n0 = tn * TN;
+  const int m0 = tm * TM, n0 = tn * TN;
   const int K = p.K;
   const int nk_all = K / BK;
   const int k_begin = (int)((int64_t)nk_all * ks / p.splitk), k_end = (int)((int64_t)nk_all * (ks + 1) / p.splitk);
   const int nk = k_end - k_begin;
 
   // Direct global -> LDS loads: load j of this wave fills the 1 KB of tile rows
-  // (64 / CH) (NW j + wave) .. + 64 / CH - 1; lane l writes row
-  // (64 / CH) (NW j + wave) + l / CH, slot l % CH, so it fetches the chunk that
-  // belongs in that slot (the CH lanes of a row cover ROW_BYTES contiguous bytes).
+  // 8 (NW j + wave) .. + 7; lane l writes row 8 (NW j + wave) + l / 8, slot l % 8,
+  // so it fetches the chunk that belongs in that slot (the 8 lanes of a row
+  // cover 128 contiguous bytes).
   const int w_rows = EPI == kGemmSwiGLU ? (p.N >> 1) : p.N;
-  const uint16_t* asrc[LOADS];
-  const uint16_t* wsrc[LOADS];
+  const uint16_t* asrc[TM / 64];
+  const uint16_t* wsrc[4];
 #pragma unroll
-  for (int j = 0; j < LOADS; ++j) {
-    const int r = (64 / CH) * (NW * j + wave) + lane / CH;
+  for (int j = 0; j < 4; ++j) {
+    const int r = 8 * (NW * j + wave) + lane / CH;
     const int c = swz(r, lane % CH);
-    const int ar = m0 + r < p.M ? m0 + r : p.M - 1;  // rows past M load a valid row; they are never stored
-    asrc[j] = p.A + (int64_t)ar * K + (int64_t)k_begin * BK + c * 8;
-    const int rt = r < TN ? r : TN - 1;  // W tile rows past the tile's columns repeat its last row
-    // weight tile row rt: for SwiGLU, each 32-row block holds the gate rows
-    // (first 16) and the up rows (last 16) of 16 outputs
+    if (j < TM / 64) {
+      const int ar = m0 + r < p.M ? m0 + r : p.M - 1;  // rows past M load a valid row; they are never stored
+      asrc[j] = p.A + (int64_t)ar * K + (int64_t)k_begin * BK + c * 8;
+    }
+    // weight tile row r (of the loads a wave issues: below TN); for SwiGLU, each
+    // 32-row block holds the gate rows (first 16) and the up rows (last 16) of 16 outputs
     int wr;
     const uint16_t* wb;
     if (EPI == kGemmSwiGLU) {
-      wr = (n0 >> 1) + 16 * (rt >> 5) + (rt & 15);
-      wb = (rt & 16) ? p.W2 : p.W;
+      wr = (n0 >> 1) + 16 * (r >> 5) + (r & 15);
+      wb = (r & 16) ? p.W2 : p.W;
     } else {
-      wr = n0 + rt;
+      wr = n0 + r;
       wb = p.W;
     }
     if (wr >= w_rows) wr = w_rows - 1;  // columns past N load a valid row; they are never stored
     wsrc[j] = wb + (int64_t)wr * K + (int64_t)k_begin * BK + c * 8;
   }
-  if (NB == 8) {
-    gemm_wave<EPI, 4, 2, LOADS>(p, smem, asrc, wsrc, nk, wave, lane, m0, n0, 128 * (wave / 4), 2 * (wave % 4), ks);
-  } else if (NB == 5) {
-    // W tile load j of wave w fills rows 8 (8 j + w) ..: rows 0..127 take
-    // loads 0 and 1 of every wave, rows 128..159 load 2 of waves 0..3
-    static_assert(LOADS == 4, "1 KB loads of 8 rows");
-    if (wave < 4) gemm_wave<EPI, 2, 3, 3>(p, smem, asrc, wsrc, nk, wave, lane, m0, n0, 64 * wave, 0, ks);
-    else gemm_wave<EPI, 2, 2, 2>(p, smem, asrc, wsrc, nk, wave, lane, m0, n0, 64 * (wave - 4), 3, ks);
-  } else if (NB == 4) {
-    gemm_wave<EPI, 2, 2, 2>(p, smem, asrc, wsrc, nk, wave, lane, m0, n0, 64 * (wave & 3), 2 * (wave >> 2), ks);
+  // W tile load j of wave w fills rows 8 (8 j + w) ..: each wave issues those below TN
+  // (NB = 7: load 3 of waves 0..3; NB = 5: load 2 of waves 0..3).
+  if constexpr (TM == 128) {
+    gemm_wave<EPI, TM, NB, 2, 2, 4>(p, smem, asrc, wsrc, nk, wave, lane, m0, n0, 64 * (wave / 4), 2 * (wave % 4), ks);
+  } else if constexpr (NB == 8) {
+    gemm_wave<EPI, TM, NB, 4, 2, 4>(p, smem, asrc, wsrc, nk, wave, lane, m0, n0, 128 * (wave / 4), 2 * (wave % 4), ks);
+  } else if constexpr (NB == 4) {
+    gemm_wave<EPI, TM, NB, 2, 2, 2>(p, smem, asrc, wsrc, nk, wave, lane, m0, n0, 64 * (wave & 3), 2 * (wave >> 2), ks);
   } else {
-#ifndef KF_GEMM_NB7_PAIRS
-#define KF_GEMM_NB7_PAIRS 0
-#endif
-    // 4-block waves and 3-block waves: 0..3 and 4..7, or even and odd
-    const bool wide = KF_GEMM_NB7_PAIRS ? (wave & 1) == 0 : wave < 4;
-    const int am0 = 64 * (KF_GEMM_NB7_PAIRS ? wave >> 1 : wave & 3);
-    // W tile load j of wave w fills rows 8 (8 j + w) ..: the last load of waves
-    // 4..7 covers rows 224..255, past the tile, and is left out.
-    static_assert(KF_GEMM_NB7_PAIRS || LOADS == 4, "waves 4..7 hold the rows past a 224-column tile");
-    if (wide) gemm_wave<EPI, 2, 4, LOADS>(p, smem, asrc, wsrc, nk, wave, lane, m0, n0, am0, 0, ks);
-    else gemm_wave<EPI, 2, 3, KF_GEMM_NB7_PAIRS ? LOADS : LOADS - 1>(p, smem, asrc, wsrc, nk, wave, lane, m0, n0, am0, 4, ks);
+    constexpr int J0 = (NB + 1) / 2, J1 = NB / 2;  // blocks of waves 0..3 and 4..7, which also issue as many loads
+    if (wave < 4) gemm_wave<EPI, TM, NB, 2, J0, J0>(p, smem, asrc, wsrc, nk, wave, lane, m0, n0, 64 * wave, 0, ks);
+    else gemm_wave<EPI, TM, NB, 2, J1, J1>(p, smem, asrc, wsrc, nk, wave, lane, m0, n0, 64 * (wave - 4), J0, ks);
   }
 }
 
@@ -544,34 +521,38 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_rows_kernel(const Params p)
 struct Tile {
   int rows, cols;
   float step_us;
-  bool few;  // gemm_rows_kernel (few rows), else gemm256_kernel
+  bool few;  // at most 128 rows of A
 };
 static constexpr Tile kTiles[] = {
-    {32, 128, 0.58f, true}, {64, 128, 0.64f, true}, {128, 128, 0.78f, true}, {128, 256, 1.17f, true},
-    {256, 128, 1.15f, false}, {256, 160, 1.35f, false}, {256, 224, 1.55f, false}, {256, 256, 1.75f, false},
+    {32, 128, 0.58f, true},   {64, 128, 0.64f, true},   {128, 128, 0.74f, true},
+    {128, 256, 1.20f, true},  {128, 256, 1.12f, false}, {256, 128, 1.10f, false},
+    {256, 160, 1.27f, false}, {256, 224, 1.65f, false}, {256, 256, 1.75f, false},
 };
+constexpr int kTileCount = sizeof(kTiles) / sizeof(kTiles[0]);
 
 // The tile and K slices of least estimated time: whole rounds of the 256 CUs
 // times a slice's K steps, 4 us for the launch, its first loads and its
-// stores, and for each slice of a split product 8 bytes per value (written
-// here, read by the consumer) at 6 TB/s.  At most eight slices (the consumers
+// stores, and for each slice 8 bytes per value (a split product's slices are
+// written here and read by the consumer, an unsplit one is added to the
+// residual) at 4.3 TB/s.  At most eight slices (the consumers
 // add no more), of at least four steps, and no more than part_elems holds.
-// Over eighteen projections of the shapes above at 20, 64, 128, 200, 512 and 2048
-// rows the choice is the fastest of all tiles and slices or within 8% of it,
-// bar three at H = 8192 (10%).
+// Over eighteen projections of the shapes above at eleven row counts from 20 to
+// 2048 the choice is the fastest of all tiles and slices or within 8% of it, bar
+// one (8192 x 8192 at 20 rows, 16%).
 GemmPlan gemm_plan(int epi, int M, int N, int K, int64_t part_elems) {
-  GemmPlan best{7, 1};
+  GemmPlan best{kTileCount - 1, 1};
   float best_us = 0.f;
   const int nk = K / BK;
-  for (int t = 0; t < (int)(sizeof(kTiles) / sizeof(kTiles[0])); ++t) {
+  for (int t = 0; t < kTileCount; ++t) {
     const Tile& T = kTiles[t];
     if (T.few && M > 128) continue;
+    if (T.rows == 128 && !T.few && M <= 128) continue;  // the few-row tile of this size streams better (108 against 116 us)
     if (t == 0 && epi == kGemmLogitsSplit) continue;  // its waves hold one 32-row block
     const int64_t tiles = (int64_t)((M + T.rows - 1) / T.rows) * ((N + T.cols - 1) / T.cols);
     for (int s = 1; s <= kGemmMaxSlices && s <= nk / 4; ++s) {
       if (s > 1 && (epi != kGemmPartialF32 || (int64_t)s * M * N > part_elems)) break;
       const float us = (float)((tiles * s + 255) / 256) * ((nk + s - 1) / s) * T.step_us + 4.f +
-                       (s > 1 ? s : 0) * (float)M * N * 8e-6f / 6.f;
+                       s * (float)M * N * 8e-6f / 4.3f;
       if (best_us == 0.f || us < best_us) {
         best_us = us;
         best = GemmPlan{t, s};
@@ -595,10 +576,11 @@ static hipError_t launch_tile(const Params& p, int tile, hipStream_t s) {
     case 1: hipLaunchKernelGGL((gemm_rows_kernel<EPI, 2, 1, 1, 4, 3>), grid, dim3(256), 0, s, p); break;
     case 2: hipLaunchKernelGGL((gemm_rows_kernel<EPI, 2, 1, 2, 4, 4>), grid, dim3(512), 0, s, p); break;
     case 3: hipLaunchKernelGGL((gemm_rows_kernel<EPI, 2, 2, 2, 4, 3>), grid, dim3(512), 0, s, p); break;
-    case 4: hipLaunchKernelGGL((gemm256_kernel<EPI, 4>), grid, dim3(kGemmThreads), 0, s, p); break;
-    case 5: hipLaunchKernelGGL((gemm256_kernel<EPI, 5>), grid, dim3(kGemmThreads), 0, s, p); break;
-    case 6: hipLaunchKernelGGL((gemm256_kernel<EPI, 7>), grid, dim3(kGemmThreads), 0, s, p); break;
-    case 7: hipLaunchKernelGGL((gemm256_kernel<EPI, 8>), grid, dim3(kGemmThreads), 0, s, p); break;
+    case 4: hipLaunchKernelGGL((gemm_tile_kernel<EPI, 128, 8>), grid, dim3(64 * NW), 0, s, p); break;
+    case 5: hipLaunchKernelGGL((gemm_tile_kernel<EPI, 256, 4>), grid, dim3(64 * NW), 0, s, p); break;
+    case 6: hipLaunchKernelGGL((gemm_tile_kernel<EPI, 256, 5>), grid, dim3(64 * NW), 0, s, p); break;
+    case 7: hipLaunchKernelGGL((gemm_tile_kernel<EPI, 256, 7>), grid, dim3(64 * NW), 0, s, p); break;
+    case 8: hipLaunchKernelGGL((gemm_tile_kernel<EPI, 256, 8>), grid, dim3(64 * NW), 0, s, p); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
