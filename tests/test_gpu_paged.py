@@ -211,3 +211,31 @@ def test_batch4_decode_with_splits_inside_pages(torch, st, which):
     print(f"splits inside pages ({which}) max row rel err", worst)
     kv.close()
     g.close()
+
+
+@pytest.mark.parametrize("off", [0, 1, 8], ids=["aligned", "off_by_one", "off_by_eight"])
+@pytest.mark.parametrize("dtype", ["float32", "bfloat16", "float16"])
+def test_kv_copy_alignments(torch, st, dtype, off):
+    """kv.write / kv.read of odd lengths across pages, from sources and to destinations that are and are not
+    16-byte aligned (8 values a thread, or one): the fp16 rounding of every value, and nothing past the ends."""
+    import ctypes
+    shape = synth.ModelShape(1, 64, 3, 3, 64, 64, 10, 1e-5, 1e4)
+    model = SeededModel(shape, 90)
+    g = st.Stage(shape, 0, 1, model.layer, None)
+    kv = g.kv(2, 400, 9)
+    n, pos0, m = 203, 61, 203 * 3 * 64
+    src = [torch.randn(m + off, device="cuda").to(getattr(torch, dtype))[off:].view(n, 3, 64) for _ in range(2)]
+    kv.write(0, 1, 0, torch.zeros(300, 3, 64, device="cuda"), torch.zeros(300, 3, 64, device="cuda"))
+    kv.write(0, 1, pos0, *src)
+    out = [torch.full((m + off + 4,), 7.0, device="cuda") for _ in range(2)]
+    kv._lib.kf_kv_read(kv.handle, 0, 1, pos0, n, *(ctypes.c_void_p(t.data_ptr() + 4 * off) for t in out))
+    whole = kv.read(0, 1, 0, 300)
+    g.sync()
+    for t, o, w in zip(src, out, whole):
+        want = t.float().half().float()
+        assert torch.equal(o[off:off + m].view(n, 3, 64), want)
+        assert (o[:off] == 7).all() and (o[off + m:] == 7).all()
+        assert torch.equal(w[pos0:pos0 + n], want)
+        assert not w[:pos0].any() and not w[pos0 + n:].any()
+    kv.close()
+    g.close()
