@@ -347,7 +347,7 @@ kf_status kf_head_argmax(kf_stage* stage, int32_t rows, const void* hidden_dev, 
  * stream, which adds a few microseconds per launch to the stream's timeline.
  */
 typedef enum {
-  KF_K_PREP = 0,       /* hidden/token input to the fp32 residual stream */
+  KF_K_PREP = 0,       /* kept for numbering: the first layer's launches read the stage input; nothing records here */
   KF_K_QKV = 1,        /* decode: RMSNorm + QKV GEMV + RoPE + KV append */
   KF_K_ATTN = 2,       /* decode: split-KV attention (partials per split) */
   KF_K_OPROJ = 3,      /* decode: merge of the partials + O GEMV + residual */

@@ -1152,36 +1152,6 @@ __global__ __launch_bounds__(256) void oproj_heads_kernel(const AttnParams a, co
 }
 
 // ------------------------------------------------------------------ small kernels
-// One thread per 4 elements of the [rows][H] input (H is a multiple of 64).
-__global__ void prep_hidden_kernel(const void* __restrict__ in, int in_bf16, const int32_t* __restrict__ tokens,
-                                   const uint16_t* __restrict__ embed, int vocab, float* __restrict__ x, int rows, int H,
-                                   int* err_flag) {
-  const int64_t i4 = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;  // index of a group of 4 elements
-  const int64_t n4 = (int64_t)rows * H / 4;
-  if (i4 >= n4) return;
-  const int row = (int)(i4 * 4 / H), k = (int)(i4 * 4 % H);
-  v4f v;
-  if (tokens) {
-    const int tok = tokens[row];
-    if (tok < 0 || tok >= vocab) {
-      if (k == 0) atomicOr(err_flag, kErrToken);
-      const float qn = __uint_as_float(0x7fc00000u);
-      v = v4f{qn, qn, qn, qn};
-    } else {
-      const uint2 e = *reinterpret_cast<const uint2*>(embed + (int64_t)tok * H + k);
-      v = v4f{__uint_as_float(e.x << 16), __uint_as_float(e.x & 0xffff0000u), __uint_as_float(e.y << 16),
-              __uint_as_float(e.y & 0xffff0000u)};
-    }
-  } else if (in_bf16) {
-    const uint2 e = reinterpret_cast<const uint2*>(in)[i4];
-    v = v4f{__uint_as_float(e.x << 16), __uint_as_float(e.x & 0xffff0000u), __uint_as_float(e.y << 16),
-            __uint_as_float(e.y & 0xffff0000u)};
-  } else {
-    v = reinterpret_cast<const v4f*>(in)[i4];
-  }
-  reinterpret_cast<v4f*>(x)[i4] = v;
-}
-
 // Second level of the greedy argmax: the per-workgroup (max, lowest row) pairs
 // of one batch row reduced by one 1024-thread workgroup.  Each thread requests
 // U = 16 pairs before comparing any, so up to 16,384 pairs per row (every LM
@@ -1272,13 +1242,6 @@ __global__ void weights_to_f16_gain_kernel(uint16_t* w, int64_t n, int K, const 
     w[i] = __builtin_bit_cast(uint16_t, h);
   }
   if (flag) atomicOr(bad, 1);
-}
-
-__global__ void store_hidden_kernel(const float* x, void* out, int out_bf16, int64_t n) {
-  const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  if (out_bf16) reinterpret_cast<uint16_t*>(out)[i] = f32_to_bf16(x[i]);
-  else reinterpret_cast<float*>(out)[i] = x[i];
 }
 
 // src [n][nkv][hd] -> the cache at positions pos0 .. pos0 + n - 1 of one user, stored as fp16.
@@ -1499,14 +1462,6 @@ hipError_t launch_oproj_heads(const AttnParams& a, const uint16_t* w, float* x, 
   return hipErrorInvalidValue;
 }
 
-hipError_t launch_prep_hidden(const void* in, int in_bf16, const int32_t* tokens, const uint16_t* embed, int vocab,
-                              float* x, int rows, int H, int* err_flag, hipStream_t s) {
-  const int64_t n4 = (int64_t)rows * H / 4;
-  hipLaunchKernelGGL(prep_hidden_kernel, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, s, in, in_bf16, tokens,
-                     embed, vocab, x, rows, H, err_flag);
-  return hipGetLastError();
-}
-
 hipError_t launch_argmax_final(const float* part_val, const int* part_idx, int n_wg, int rows, int32_t* token,
                                float* max_logit, hipStream_t s) {
   hipLaunchKernelGGL(argmax_final_kernel, dim3(rows), dim3(1024), 0, s, part_val, part_idx, n_wg, token, max_logit);
@@ -1533,12 +1488,6 @@ hipError_t launch_weights_to_f16_gain(uint16_t* w, int64_t n, int K, const uint1
   const int64_t blocks = (n + 255) / 256;
   hipLaunchKernelGGL(weights_to_f16_gain_kernel, dim3((unsigned)(blocks < 8192 ? blocks : 8192)), dim3(256), 0, s, w, n, K,
                      g, bad);
-  return hipGetLastError();
-}
-
-hipError_t launch_store_hidden(const float* x, void* out, int out_bf16, int64_t n, hipStream_t s) {
-  const int64_t blocks = (n + 255) / 256;
-  hipLaunchKernelGGL(store_hidden_kernel, dim3((unsigned)blocks), dim3(256), 0, s, x, out, out_bf16, n);
   return hipGetLastError();
 }
 

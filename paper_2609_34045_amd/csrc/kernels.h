@@ -176,8 +176,6 @@ hipError_t launch_attn_decode(const AttnParams& p, int batch, hipStream_t s);
 hipError_t launch_attn_merge(const AttnParams& p, uint16_t* o16, float* o32, int batch, hipStream_t s);
 // x[b][0:N) += W_o o_b with o_b merged from the attention partials in p (W_o [N][nq*hd] fp16).
 hipError_t launch_oproj_heads(const AttnParams& p, const uint16_t* w, float* x, int N, int batch, hipStream_t s);
-hipError_t launch_prep_hidden(const void* in, int in_bf16, const int32_t* tokens, const uint16_t* embed, int vocab,
-                              float* x, int rows, int H, int* err_flag, hipStream_t s);
 hipError_t launch_argmax_final(const float* part_val, const int* part_idx, int n_wg, int rows, int32_t* token,
                                float* max_logit, hipStream_t s);
 // In place over n elements: bf16 weights to fp16 (round to nearest even); *bad |= 1
@@ -187,7 +185,6 @@ hipError_t launch_weights_to_f16(uint16_t* w, int64_t n, int* bad, hipStream_t s
 hipError_t launch_gain_fold_check(const uint16_t* w, int64_t n, int K, const uint16_t* g, int* flag, hipStream_t s);
 // In place: bf16 w[r][k] -> fp16 w[r][k] g[k] (the gain folded into the columns); *bad on an fp16 overflow.
 hipError_t launch_weights_to_f16_gain(uint16_t* w, int64_t n, int K, const uint16_t* g, int* bad, hipStream_t s);
-hipError_t launch_store_hidden(const float* x, void* out, int out_bf16, int64_t n, hipStream_t s);
 // Positions [pos0, pos0 + n) of one user in one layer (k, v: the layer's base)
 // from / to [n][nkv][hd] rows.  src_type: 0 fp32, 1 bf16, 2 fp16 (the kf_dtype values).
 hipError_t launch_kv_write(uint16_t* k, uint16_t* v, const KvPages& kp, int user, int pos0, const void* src_k,

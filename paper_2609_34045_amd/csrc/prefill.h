@@ -27,6 +27,12 @@ struct PrefillLayer {
   uint16_t* vc;
   void* out;     // hidden output after this layer (last layer only), else NULL
   int out_bf16;
+  // The stage's input (first layer only; exactly one set): hidden rows, fp32 or bf16, or token ids, rows of embed
+  const void* src;
+  int src_bf16;
+  const int32_t* tokens;
+  const uint16_t* embed;
+  int vocab;
 };
 
 // Matrix-core GEMM of the prefill projections (gemm.hip); K must be a multiple

@@ -57,60 +57,115 @@ __device__ __forceinline__ f32x16 mfma32(v4u a, v4u b, f32x16 c) {
 
 // ------------------------------------------------------------------ row RMSNorm -> fp16
 // Row RMSNorm of the residual stream to fp16 (gain g, or none when g is NULL:
-// the gain is then folded into the next projection's weights).  With nsplit > 0 the row first
-// takes the nsplit split-K slices of the projection that just ran (part, slice
-// stride `stride`), added in slice order, and the sum is written back to x.
-// Threads move 16 bytes at a time and request every slice before adding; the
-// row loops are unrolled by 4, so the loads of four 16-byte steps are in flight
-// together (70B-shaped rows: 24.6 -> 21.1 us per norm).
+// the gain is then folded into the next projection's weights).  The row first
+// takes the NS split-K slices of the projection that just ran (part, slice
+// stride `stride`), added in slice order; with SRC it is the stage's input (fp32
+// or bf16 rows, or the embedding rows of tokens), which starts the residual
+// stream.  Either way the sum is written back to x.
+// Bound by the copy at hundreds of rows and by one memory round trip at few: a
+// thread requests every 16-byte piece of its row and of the slices before it
+// adds any, and holds the row in registers from the sum of squares to the store
+// (rows past BS x NV pieces go through x again).  8B shape: a norm over 8 slices of
+// 200 rows 12.6 -> 8.7 us against 256 threads that read the row twice, the input
+// copied by a launch of its own and normed 10.4 -> 6.3 us; at 1500 rows 20.8 ->
+// 20.0 us and 20.8 -> 16.1 us.
 constexpr int kMaxSlices = kGemmMaxSlices;
 
-__global__ __launch_bounds__(256) void rmsnorm_rows_f16_kernel(float* __restrict__ x, const float* __restrict__ part, int nsplit,
-                                                                int64_t stride, const uint16_t* __restrict__ g, float eps,
-                                                                uint16_t* __restrict__ out, int H, int* err_flag) {
+struct RowSource {
+  const void* in;  // [T][H] fp32 or (bf16) bf16 rows, or NULL
+  int bf16;
+  const int32_t* tokens;  // [T] ids: rows of embed [vocab][H] bf16
+  const uint16_t* embed;
+  int vocab;
+};
+
+// Values 4 k .. + 3 of input row `row`; NaN for a token outside [0, vocab).
+__device__ __forceinline__ v4f source_piece(const RowSource& s, int row, int k, int H4, int tok) {
+  const uint2* h = nullptr;
+  if (s.tokens) {
+    if (tok < 0 || tok >= s.vocab) {
+      const float qn = __uint_as_float(0x7fc00000u);
+      return v4f{qn, qn, qn, qn};
+    }
+    h = reinterpret_cast<const uint2*>(s.embed) + (int64_t)tok * H4 + k;
+  } else if (s.bf16) {
+    h = reinterpret_cast<const uint2*>(s.in) + (int64_t)row * H4 + k;
+  } else {
+    return reinterpret_cast<const v4f*>(s.in)[(int64_t)row * H4 + k];
+  }
+  const uint2 e = *h;
+  return v4f{__uint_as_float(e.x << 16), __uint_as_float(e.x & 0xffff0000u), __uint_as_float(e.y << 16),
+             __uint_as_float(e.y & 0xffff0000u)};
+}
+
+template <int BS, int NV, int NS, bool SRC>
+__global__ __launch_bounds__(BS) void rmsnorm_rows_f16_kernel(float* __restrict__ x, const float* __restrict__ part,
+                                                              int64_t stride, const RowSource src,
+                                                              const uint16_t* __restrict__ g, float eps,
+                                                              uint16_t* __restrict__ out, int H, int* err_flag) {
   const int row = blockIdx.x, tid = threadIdx.x, H4 = H / 4;
   v4f* xr = reinterpret_cast<v4f*>(x + (int64_t)row * H);
   const v4f* pr = reinterpret_cast<const v4f*>(part + (int64_t)row * H);
   const int64_t st4 = stride / 4;
+  const int tok = SRC && src.tokens ? src.tokens[row] : 0;
+  if (SRC && src.tokens && tid == 0 && (tok < 0 || tok >= src.vocab)) atomicOr(err_flag, kErrToken);
   float ss = 0.f;
-#pragma unroll 4
-  for (int k = tid; k < H4; k += 256) {
-    v4f v = xr[k];
-    if (nsplit > 0) {
-      v4f sl[kMaxSlices];
+  // the piece at k: requested, and (with the slices) added and written back
+  auto request = [&](int k, v4f& v, v4f (&sl)[NS + 1]) {
+    v = SRC ? source_piece(src, row, k, H4, tok) : xr[k];
 #pragma unroll
-      for (int i = 0; i < kMaxSlices; ++i)
-        if (i < nsplit) sl[i] = pr[i * st4 + k];
+    for (int i = 0; i < NS; ++i) sl[i] = pr[i * st4 + k];
+  };
+  auto take = [&](int k, v4f& v, const v4f (&sl)[NS + 1]) {
 #pragma unroll
-      for (int i = 0; i < kMaxSlices; ++i)
-        if (i < nsplit) v += sl[i];
-      xr[k] = v;
-    }
+    for (int i = 0; i < NS; ++i) v += sl[i];
+    if (SRC || NS > 0) xr[k] = v;
     ss += (v.x * v.x + v.y * v.y) + (v.z * v.z + v.w * v.w);
+  };
+  v4f v[NV], sl[NV][NS + 1];
+#pragma unroll
+  for (int i = 0; i < NV; ++i)
+    if (tid + i * BS < H4) request(tid + i * BS, v[i], sl[i]);
+#pragma unroll
+  for (int i = 0; i < NV; ++i)
+    if (tid + i * BS < H4) take(tid + i * BS, v[i], sl[i]);
+  for (int k = tid + NV * BS; k < H4; k += BS) {
+    v4f w, sw[NS + 1];
+    request(k, w, sw);
+    take(k, w, sw);
   }
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) ss += __shfl_xor(ss, o);
-  __shared__ float red[4];
+  __shared__ float red[BS / 64];
   if ((tid & 63) == 0) red[tid >> 6] = ss;
   __syncthreads();
-  const float rs = 1.0f / sqrtf(((red[0] + red[1]) + (red[2] + red[3])) / (float)H + eps);
+  ss = 0.f;
+#pragma unroll
+  for (int i = 0; i < BS / 64; ++i) ss += red[i];
+  const float rs = 1.0f / sqrtf(ss / (float)H + eps);
   uint2* o = reinterpret_cast<uint2*>(out + (int64_t)row * H);
   const uint2* g4 = reinterpret_cast<const uint2*>(g);
   bool bad = false;
-#pragma unroll 4
-  for (int k = tid; k < H4; k += 256) {
-    const v4f v = xr[k] * rs;
+  auto put = [&](int k, v4f w) {
+    w *= rs;
     const uint2 gw = g4 ? g4[k] : uint2{0x3F803F80u, 0x3F803F80u};  // g NULL: folded into the next matrix (gain 1)
-    o[k] = uint2{pack_f16_checked(v.x * __uint_as_float(gw.x << 16), v.y * __uint_as_float(gw.x & 0xffff0000u), bad),
-                 pack_f16_checked(v.z * __uint_as_float(gw.y << 16), v.w * __uint_as_float(gw.y & 0xffff0000u), bad)};
-  }
+    o[k] = uint2{pack_f16_checked(w.x * __uint_as_float(gw.x << 16), w.y * __uint_as_float(gw.x & 0xffff0000u), bad),
+                 pack_f16_checked(w.z * __uint_as_float(gw.y << 16), w.w * __uint_as_float(gw.y & 0xffff0000u), bad)};
+  };
+#pragma unroll
+  for (int i = 0; i < NV; ++i)
+    if (tid + i * BS < H4) put(tid + i * BS, v[i]);
+  for (int k = tid + NV * BS; k < H4; k += BS) put(k, xr[k]);
   raise_err(err_flag, bad, kErrF16Range);
 }
 
 // ------------------------------------------------------------------ RoPE + KV append
 // QKV [T][(nq+2nkv) hd] fp32, the sum of nsplit split-K slices of `qkv` (slice
 // stride `stride`) -> q [T][nq][hd] fp16 (rotated), K/V cache at pos0 + i (fp16).
-// A thread takes 4 consecutive rotation pairs (j .. j+3, j+hd/2 .. j+hd/2+3).
+// A thread takes 4 consecutive rotation pairs (j .. j+3, j+hd/2 .. j+hd/2+3), one
+// item: grid.y covers a token's items, so that a few tokens fill the chip (with
+// a workgroup per token that walked them 37 Qwen3-8B-shaped tokens took 7.7 us,
+// so 5.0; 1500 tokens of the 8B shape 14.9 either way).
 // With gq / gk set (blocks with per-head q / k norms), each q and k head is
 // RMS-normalised over its hd values first: the hd/8 consecutive threads that
 // hold a head add their squares with lane shuffles.
@@ -123,7 +178,8 @@ __global__ __launch_bounds__(256) void rope_kv_kernel(const float* qkv, int nspl
   const int nh = nq + 2 * nkv;
   const float* src = qkv + (int64_t)i * nh * hd;
   bool bad = false;
-  for (int e = threadIdx.x; e < nh * q4; e += 256) {
+  const int e = blockIdx.y * 256 + threadIdx.x;
+  if (e < nh * q4) {  // a head's q4 (8 or 16) threads are in one wave and in range together
     const int h = e / q4, j = (e % q4) * 4;
     v4f a = {0.f, 0.f, 0.f, 0.f}, b = {0.f, 0.f, 0.f, 0.f};
     {
@@ -675,7 +731,8 @@ __global__ __launch_bounds__(256) void attn_prefill_combine_kernel(const float* 
 
 // ------------------------------------------------------------------ final copy
 // Hidden output of the stage: the residual stream plus the nsplit pending
-// split-K slices of the last down projection (slice stride n).
+// split-K slices of the last down projection (slice stride n).  One value a
+// thread: four were slower (8B-shaped 1500 rows of two slices 23.2 -> 27.6 us).
 __global__ void store_rows_kernel(const float* x, const float* part, int nsplit, void* out, int out_bf16,
                                   int64_t n) {
   const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
@@ -830,6 +887,37 @@ hipError_t prefill_reserve(PrefillWorkspace& ws, const PrefillArgs& a) {
   return hipSuccess;
 }
 
+// The row norm that follows the residual stream's `slices` pending slices, or the
+// stage's input: 1024 threads a row (8 KB of it each way per pass of the
+// workgroup), 256 below H = 2048, where most of 1024 would idle (H = 512, 1500
+// rows: 7.0 against 4.7 us).
+template <int NS, bool SRC>
+static hipError_t launch_rmsnorm_ns(PrefillWorkspace& ws, const PrefillArgs& a, const RowSource& src, const uint16_t* g) {
+  if (a.H >= 2048)
+    hipLaunchKernelGGL((rmsnorm_rows_f16_kernel<1024, 2, NS, SRC>), dim3(a.T), dim3(1024), 0, a.stream, ws.x, ws.part,
+                       (int64_t)a.T * a.H, src, g, a.eps, ws.xn, a.H, a.err_flag);
+  else
+    hipLaunchKernelGGL((rmsnorm_rows_f16_kernel<256, 2, NS, SRC>), dim3(a.T), dim3(256), 0, a.stream, ws.x, ws.part,
+                       (int64_t)a.T * a.H, src, g, a.eps, ws.xn, a.H, a.err_flag);
+  return hipGetLastError();
+}
+static hipError_t launch_rmsnorm(PrefillWorkspace& ws, const PrefillArgs& a, int slices, const RowSource* src,
+                                 const uint16_t* g) {
+  const RowSource none{};
+  if (src) return slices ? hipErrorInvalidValue : launch_rmsnorm_ns<0, true>(ws, a, *src, g);
+  switch (slices) {
+    case 0: return launch_rmsnorm_ns<0, false>(ws, a, none, g);
+    case 2: return launch_rmsnorm_ns<2, false>(ws, a, none, g);
+    case 3: return launch_rmsnorm_ns<3, false>(ws, a, none, g);
+    case 4: return launch_rmsnorm_ns<4, false>(ws, a, none, g);
+    case 5: return launch_rmsnorm_ns<5, false>(ws, a, none, g);
+    case 6: return launch_rmsnorm_ns<6, false>(ws, a, none, g);
+    case 7: return launch_rmsnorm_ns<7, false>(ws, a, none, g);
+    case 8: return launch_rmsnorm_ns<8, false>(ws, a, none, g);
+    default: return hipErrorInvalidValue;
+  }
+}
+
 hipError_t prefill_layer(PrefillWorkspace& ws, const PrefillArgs& a, const PrefillLayer& l, const Tracer& tr) {
   hipStream_t s = a.stream;
   const int T = a.T, H = a.H, nqkv = (a.nq + 2 * a.nkv) * a.hd;
@@ -839,17 +927,17 @@ hipError_t prefill_layer(PrefillWorkspace& ws, const PrefillArgs& a, const Prefi
   enum { NORM = 8, QKV = 9, ROPE = 10, ATTN = 11, OPROJ = 12, GATEUP = 13, DOWN = 14, STORE = 15 };
   // The previous layer's down projection may still be pending as split-K slices.
   tr.begin(NORM);
-  hipLaunchKernelGGL(rmsnorm_rows_f16_kernel, dim3(T), dim3(256), 0, s, ws.x, ws.part, ws.pending, TH, l.g_attn,
-                     a.eps, ws.xn, H, a.err_flag);
+  const RowSource src{l.src, l.src_bf16, l.tokens, l.embed, l.vocab};
+  e = launch_rmsnorm(ws, a, ws.pending, l.src || l.tokens ? &src : nullptr, l.g_attn);
   tr.end(NORM);
   ws.pending = 0;
-  if ((e = hipGetLastError()) != hipSuccess) return e;
+  if (e != hipSuccess) return e;
   tr.begin(QKV);
   e = launch_gemm(kGemmPartialF32, ws.qkv, ws.xn, l.wqkv, nullptr, T, nqkv, H, ws.part, nullptr, a.err_flag, s);
   tr.end(QKV);
   if (e != hipSuccess) return e;
   tr.begin(ROPE);
-  hipLaunchKernelGGL(rope_kv_kernel, dim3(T), dim3(256), 0, s, ws.part, ws.qkv.slices, (int64_t)T * nqkv, ws.q, l.kc, l.vc,
+  hipLaunchKernelGGL(rope_kv_kernel, dim3(T, ((a.nq + 2 * a.nkv) * (a.hd / 8) + 255) / 256), dim3(256), 0, s, ws.part, ws.qkv.slices, (int64_t)T * nqkv, ws.q, l.kc, l.vc,
                      a.kv, a.user, a.rope_cos, a.rope_sin, a.nq, a.nkv, a.hd, a.pos0, l.g_qn, l.g_kn, a.eps,
                      a.err_flag);
   tr.end(ROPE);
@@ -898,10 +986,9 @@ hipError_t prefill_layer(PrefillWorkspace& ws, const PrefillArgs& a, const Prefi
   int pend_o = 0;
   if ((e = resid_proj(OPROJ, ws.oproj, ws.o, l.wo, a.nq * a.hd, &pend_o)) != hipSuccess) return e;
   tr.begin(NORM);
-  hipLaunchKernelGGL(rmsnorm_rows_f16_kernel, dim3(T), dim3(256), 0, s, ws.x, ws.part, pend_o, TH, l.g_mlp, a.eps,
-                     ws.xn, H, a.err_flag);
+  e = launch_rmsnorm(ws, a, pend_o, nullptr, l.g_mlp);
   tr.end(NORM);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
+  if (e != hipSuccess) return e;
   tr.begin(GATEUP);
   e = launch_gemm(kGemmSwiGLU, ws.gateup, ws.xn, l.wg, l.wu, T, 2 * a.F, H, nullptr,
                   ws.act, a.err_flag, s);

@@ -1229,12 +1229,6 @@ static kf_status prefill_impl(kf_stage* s, kf_kv* kv, int32_t user, int32_t pos0
   const kf_status gst = kv_grant(kv, 1, &user, &upto);
   if (gst != KF_OK) return gst;
   const Tracer tr = no_alloc ? Tracer{} : s->tracer();  // event records may create events
-  tr.begin(KF_K_PREP);
-  hipError_t e = launch_prep_hidden(hidden_in_dev, io == KF_BF16, tokens_dev, s->embed, c.vocab, ws->x, n, c.hidden,
-                                    s->err_flag, s->stream);
-  tr.end(KF_K_PREP);
-  KF_HIP(e, "prefill prep launch");
-  ws->pending = 0;  // x now holds the whole input; no split-K slices are pending
   for (int l = s->lo; l < s->hi; ++l) {
     const LayerW& L = s->layers[l - s->lo];
     const int64_t loff = (l - s->lo) * kv->layer_stride;
@@ -1250,6 +1244,13 @@ static kf_status prefill_impl(kf_stage* s, kf_kv* kv, int32_t user, int32_t pos0
     pl.g_kn = L.g_kn;
     pl.kc = kv->k + loff;
     pl.vc = kv->v + loff;
+    if (l == s->lo) {  // the first layer's norm reads the stage's input and starts the residual stream
+      pl.src = hidden_in_dev;
+      pl.src_bf16 = io == KF_BF16;
+      pl.tokens = tokens_dev;
+      pl.embed = s->embed;
+      pl.vocab = c.vocab;
+    }
     pl.out = l == s->hi - 1 ? hidden_out_dev : nullptr;
     pl.out_bf16 = io == KF_BF16;
     KF_HIP(prefill_layer(*ws, pa, pl, tr), "prefill layer");

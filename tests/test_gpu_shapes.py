@@ -250,3 +250,31 @@ def test_prefill_short_chunk_over_long_cache(torch, st, nq, nkv, hd, T):
     print(f"G={nq // nkv} hd={hd} T={T} over {n0} keys: max row rel err of the addition", err)
     kv.close()
     g.close()
+
+
+@pytest.mark.parametrize("H", [1984, 2048, 8192, 8320])
+@pytest.mark.parametrize("io", ["tokens", "bfloat16", "float32"])
+def test_prefill_row_norm_widths(torch, st, H, io):
+    """The prefill's row norm around its row sizes (256 or 1024 threads, the row in registers up to H = 8192,
+    the rest through memory), on each kind of stage input; compared with what the float64 oracle's layer adds."""
+    shape = synth.ModelShape(1, H, 2, 1, 64, 192, 50, 1e-5, 1e4)
+    cfg, T = 95, 3
+    model = SeededModel(shape, cfg)
+    head = model.head() if io == "tokens" else None
+    g = st.Stage(shape, 0, 1, model.layer, head)
+    o = OracleStage(shape, 0, 1, model.layer, head, max_users=1, max_ctx=T)
+    kv = g.kv(1, T)
+    if io == "tokens":
+        toks = synth.tokens(cfg, 0, T, shape.vocab)
+        y, ref = g.prefill(kv, 0, 0, tokens=torch.from_numpy(toks).cuda()), o.prefill(0, 0, tokens=toks)
+        x = (head["embed"][toks].astype(np.uint32) << 16).view(np.float32).astype(np.float64)
+    else:
+        t = torch.from_numpy(synth.hidden_states(cfg, synth.STREAM_PREFILL_HIDDEN, 0, T, H)).to(getattr(torch, io))
+        x = host(t)
+        y, ref = g.prefill(kv, 0, 0, hidden=t.cuda()), o.prefill(0, 0, hidden=x)
+    # bf16 rows come back rounded to 2^-9 of their values, the additions are about a twentieth of them
+    rtol = 2 ** -9 * np.max(np.abs(ref)) / np.min(np.max(np.abs(ref - x), axis=1)) + 5e-3 if io == "bfloat16" else 5e-3
+    err = assert_hidden_close(host(y) - x, ref - x, rtol=rtol, what=f"H {H} {io}")
+    print(f"H={H} {io} max row rel err of the addition", err, "of", rtol)
+    kv.close()
+    g.close()
