@@ -178,8 +178,10 @@ __global__ __launch_bounds__(256) void rope_kv_kernel(const float* qkv, int nspl
   const int nh = nq + 2 * nkv;
   const float* src = qkv + (int64_t)i * nh * hd;
   bool bad = false;
-  const int e = blockIdx.y * 256 + threadIdx.x;
-  if (e < nh * q4) {  // a head's q4 (8 or 16) threads are in one wave and in range together
+  // A head's q4 threads, 8 or 16, are in one wave and in range together.  One
+  // pass: written as an `if`, the same body compiled to a kernel that took 17.2
+  // us against 7.4 (200 tokens, 5 slices).
+  for (int e = blockIdx.y * 256 + threadIdx.x; e < nh * q4; e += gridDim.y * 256) {
     const int h = e / q4, j = (e % q4) * 4;
     v4f a = {0.f, 0.f, 0.f, 0.f}, b = {0.f, 0.f, 0.f, 0.f};
     {
