@@ -1375,6 +1375,10 @@ hipError_t launch_gemv_src(int epi, int R, int U, bool norm, const GemvParams& p
   if ((p.src == nullptr) == (p.tokens == nullptr)) return hipErrorInvalidValue;
   const int grid = gemv_grid(epi, R, p);
   if (R == 8 && U == 1) return gemv_dispatch_b<8, 1, true>(epi, norm, p, grid, s);
+  if (R == 4 && U == 1 && epi == kEpiQKV && p.batch == 1 && norm) {  // as for the later layers (launch_gemv)
+    gemv_norm_launch<1, 4, 1, kEpiQKV, true, false>(p, grid, s);
+    return hipGetLastError();
+  }
   return hipErrorInvalidValue;
 }
 

@@ -23,7 +23,7 @@ using namespace kf;
 // 4 or 10 for the residual launches where the grid then fills whole rounds of the CUs) and one
 // 16-byte chunk per row in flight per thread (two were slower at every batch).
 constexpr int kGemvRows = 8, kGemvChunks = 1;
-constexpr int kQkvRowsBatch1 = 4;  // the batch-1 QKV launch (after the first layer) takes 4-row workgroups
+constexpr int kQkvRowsBatch1 = 4;  // the batch-1 QKV launch takes 4-row workgroups
 // The LM head on the rows a decode kept (fp16, batch 2-4) takes 12-row
 // workgroups: each reads its input rows once for all its weight rows, so these
 // move two thirds of the 8-row launch's input bytes per weight byte (8B-shaped
@@ -958,7 +958,7 @@ kf_status kf_stage_decode(kf_stage* s, kf_kv* kv, int32_t batch, const int32_t* 
       g.vocab = c.vocab;
       g.x_init = s->x;
       g.in16 = 0;  // the input rows come from src / tokens
-      le = launch_gemv_src(kEpiQKV, kGemvRows, kGemvChunks, true, g, st);
+      le = launch_gemv_src(kEpiQKV, batch == 1 ? kQkvRowsBatch1 : kGemvRows, kGemvChunks, true, g, st);
     } else {
       le = launch_gemv(kEpiQKV, batch == 1 ? kQkvRowsBatch1 : kGemvRows, kGemvChunks, true, g, st);
     }
