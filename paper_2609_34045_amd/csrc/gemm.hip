@@ -526,7 +526,7 @@ struct Tile {
 static constexpr Tile kTiles[] = {
     {32, 128, 0.58f, true},   {64, 128, 0.64f, true},   {128, 128, 0.74f, true},
     {128, 256, 1.20f, true},  {128, 256, 1.12f, false}, {256, 128, 1.10f, false},
-    {256, 160, 1.27f, false}, {256, 224, 1.65f, false}, {256, 256, 1.75f, false},
+    {256, 160, 1.32f, false}, {256, 224, 1.65f, false}, {256, 256, 1.75f, false},
 };
 constexpr int kTileCount = sizeof(kTiles) / sizeof(kTiles[0]);
 
@@ -534,7 +534,7 @@ constexpr int kTileCount = sizeof(kTiles) / sizeof(kTiles[0]);
 // times a slice's K steps, 4 us for the launch, its first loads and its
 // stores, and for each slice 8 bytes per value (a split product's slices are
 // written here and read by the consumer, an unsplit one is added to the
-// residual) at 4.3 TB/s.  At most eight slices (the consumers
+// residual) at 5 TB/s.  At most eight slices (the consumers
 // add no more), of at least four steps, and no more than part_elems holds.
 // Over eighteen projections of the shapes above at eleven row counts from 20 to
 // 2048 the choice is the fastest of all tiles and slices or within 8% of it, bar
@@ -549,10 +549,10 @@ GemmPlan gemm_plan(int epi, int M, int N, int K, int64_t part_elems) {
     if (T.rows == 128 && !T.few && M <= 128) continue;  // the few-row tile of this size streams better (108 against 116 us)
     if (t == 0 && epi == kGemmLogitsSplit) continue;  // its waves hold one 32-row block
     const int64_t tiles = (int64_t)((M + T.rows - 1) / T.rows) * ((N + T.cols - 1) / T.cols);
-    for (int s = 1; s <= kGemmMaxSlices && s <= nk / 4; ++s) {
-      if (s > 1 && (epi != kGemmPartialF32 || (int64_t)s * M * N > part_elems)) break;
+    for (int s = 1; s <= kGemmMaxSlices; ++s) {
+      if (s > 1 && (s > nk / 4 || epi != kGemmPartialF32 || (int64_t)s * M * N > part_elems)) break;
       const float us = (float)((tiles * s + 255) / 256) * ((nk + s - 1) / s) * T.step_us + 4.f +
-                       s * (float)M * N * 8e-6f / 4.3f;
+                       s * (float)M * N * 8e-6f / 5.f;
       if (best_us == 0.f || us < best_us) {
         best_us = us;
         best = GemmPlan{t, s};
