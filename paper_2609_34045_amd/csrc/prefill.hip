@@ -804,15 +804,23 @@ static int64_t other_bytes(const PrefillArgs& a) {
 
 int64_t prefill_ws_bytes(const PrefillArgs& a) { return other_bytes(a) + a256(sized_part(a, a.T) * 4); }
 
+// Values that the most slices and key splits a plan takes would fill.
+constexpr int kMaxKeySplits = 64;
+static int64_t most_part(const PrefillArgs& a) {
+  const int64_t T = a.T, nqkv = (int64_t)(a.nq + 2 * a.nkv) * a.hd;
+  return std::max(kMaxSlices * T * std::max(nqkv, (int64_t)a.H), kMaxKeySplits * T * a.nq * (a.hd + 2));
+}
+
 // Space for partial sums that a chunk's plan may use: what the sizing rule
 // gives, raised to kPartSmall for a chunk that fits the scratch array (as far
 // as the array goes, so that the same chunk gets the same plan, and so the
-// same bits, wherever its workspace lies) and to kPartLarge for others.
+// same bits, wherever its workspace lies) and to kPartLarge for others, but no
+// more than a plan can fill.
 constexpr int64_t kPartSmall = 48LL << 20, kPartLarge = 256LL << 20;
 static int64_t part_bytes(const PrefillArgs& a) {
-  const int64_t sized = a256(sized_part(a, a.T) * 4), other = other_bytes(a);
-  if (other + sized > kPrefillScratchBytes) return std::max(sized, kPartLarge);
-  return std::max(sized, std::min(kPartSmall, kPrefillScratchBytes - other));
+  const int64_t sized = a256(sized_part(a, a.T) * 4), most = a256(most_part(a) * 4), other = other_bytes(a);
+  if (other + sized > kPrefillScratchBytes) return std::max(sized, std::min(kPartLarge, most));
+  return std::max(sized, std::min(std::min(kPartSmall, most), kPrefillScratchBytes - other));
 }
 
 // Key splits of the attention of least estimated time: the blocks of a split
@@ -825,7 +833,7 @@ static int attn_splits(const PrefillArgs& a, int64_t part_elems) {
   const int64_t elems = (int64_t)a.T * a.nq * (a.hd + 2);  // partials of one split
   int best = 1;
   float best_us = 0.f;
-  for (int z = 1; z <= 64 && z <= (nblk + 1) / 2; ++z) {
+  for (int z = 1; z <= kMaxKeySplits && z <= (nblk + 1) / 2; ++z) {
     if (z > 1 && z * elems > part_elems) break;
     const int64_t wgs = tiles * z, rest = wgs % 512;
     const float rounds = (float)(wgs / 512) * 2.6f + (rest == 0 ? 0.f : rest <= 256 ? 1.7f : 2.6f);
@@ -870,7 +878,7 @@ hipError_t prefill_reserve(PrefillWorkspace& ws, const PrefillArgs& a) {
   int64_t part = part_bytes(a);
   PrefillArgs b = a;
   for (b.T = 256; b.T < a.T; b.T += 256) part = std::max(part, part_bytes(b));
-  const int64_t total = other_bytes(a) + std::max(part, kPartSmall);
+  const int64_t total = other_bytes(a) + std::max(part, std::min(kPartSmall, a256(most_part(a) * 4)));
   if (total > ws.cap) {
     char* mem = nullptr;
     // Drain work that may still use the old buffer before freeing it.
