@@ -316,6 +316,9 @@ kf_status kf_stage_prefill_noalloc(kf_stage* stage, kf_kv* kv, int32_t user, int
  * embedding and unembedding and samples after the model's last block):
  * logits_dev fp32 [rows, V] = RMSNorm(hidden; final gain) x LM_head^T, for hidden_dev
  * [rows, H] in dtype (KF_F32 or KF_BF16), any rows >= 1.  Head stages only (else KF_ESTATE).
+ * Equal LM-head rows give exactly equal logits.  Up to four rows and more rows sum in
+ * different orders (the last bits of a row's logits may differ between the two); among
+ * calls of more than four, a row's logits have the same bits whatever the count.
  * hidden_dev NULL: the rows the stage's last kf_stage_decode kept (its hidden_out_dev
  * was NULL); rows must equal that decode's batch and dtype is ignored (else KF_ESTATE,
  * also when the last decode returned its rows or failed).

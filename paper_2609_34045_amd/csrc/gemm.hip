@@ -90,12 +90,14 @@ struct Params {
   int* err_flag;
   int rows_out;            // logits: rows of the output (M counts the rows of A)
   const float* row_scale;  // logits: factor of each output row
+  int kstride;             // logits: K steps are taken in the order 0, kstride, 2 kstride, .. (mod their number)
 };
 
 // Rows of A per output row: the logits of fp32 rows take each row as two fp16
 // parts, in 32-row blocks of high parts, each followed by the block of the low
 // parts, that add into one accumulator.
 constexpr int parts_of(int epi) { return epi == kGemmLogitsSplit ? 2 : 1; }
+constexpr bool is_logits(int epi) { return epi == kGemmLogits || epi == kGemmLogitsSplit; }
 
 // Large tiles: TM rows (256 or 128) x 32 NB columns, eight waves (two per SIMD).
 // LDS ring depths: activation loads run up to ring_a K steps ahead, weight
@@ -139,7 +141,7 @@ __device__ __forceinline__ void store_tile(const Params& p, const f32x16 (&acc)[
         }
       }
     raise_err(p.err_flag, bad, kErrF16Range);
-  } else if (EPI == kGemmLogits || EPI == kGemmLogitsSplit) {
+  } else if (is_logits(EPI)) {
     bool nan = false;
 #pragma unroll
     for (int i = 0; i < MB; ++i)
@@ -194,11 +196,14 @@ __device__ __forceinline__ void gemm_wave(const Params& p, uint8_t* smem, const 
   constexpr int NL = LA + LW;     // direct loads per slice that carries them
   static_assert(RD <= SLOTS && LW <= 4, "a slice's slots issue its reads");
 
-  // Step kt's stages; past the last step a load fetches step nk-1 again (into
-  // the stage of the step it stands in for, which is never read).
+  // Step kt's stages and source; past the last step a load fetches step nk-1 (logits:
+  // an earlier step) again, into the stage of the step it stands in for, which is never read.
   auto abuf = [&](int kt) { return smem + (kt % SA) * a_stage(TM); };
   auto wbuf = [&](int kt) { return smem + SA * a_stage(TM) + (kt % SW) * w_stage(NB); };
-  auto src_step = [&](int kt) { return (int64_t)(kt < nk ? kt : nk - 1) * BK; };
+  auto src_step = [&](int kt) {
+    if (is_logits(EPI)) return (int64_t)((unsigned)(kt * p.kstride) % (unsigned)nk) * BK;
+    return (int64_t)(kt < nk ? kt : nk - 1) * BK;
+  };
   // (named operands: the host pass drops the kernel's launch stub when the
   // builtin's pointer argument is a call expression)
   auto load_one = [&](bool w, int j, int kt) {
@@ -440,11 +445,12 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_rows_kernel(const Params p)
   // around, as do those whose slices begin at multiples of 4 KB within a row: all
   // at the same offset of rows a power of two apart, they press on a few memory
   // channels at a time (8B-shaped gate/up over 32 rows: 50.9 -> 40.7 us, with the
-  // weights loaded non-temporally; 64 rows 53.3 -> 44.2).
-  const int rot = p.splitk == 1 || (nk * RB) % 4096 == 0 ? (int)(((unsigned)t * 13u) % (unsigned)nk) : 0;
+  // weights loaded non-temporally; 64 rows 53.3 -> 44.2).  Logits keep one order
+  // in every tile (logits_kstride).
+  const int rot = !is_logits(EPI) && (p.splitk == 1 || (nk * RB) % 4096 == 0) ? (int)(((unsigned)t * 13u) % (unsigned)nk) : 0;
   auto issue = [&](int k) {
     uint8_t* st = smem + (k % D) * STAGE;
-    const int kk = k + rot < nk ? k + rot : k + rot - nk;
+    const int kk = is_logits(EPI) ? (int)((unsigned)(k * p.kstride) % (unsigned)nk) : k + rot < nk ? k + rot : k + rot - nk;
 #pragma unroll
     for (int j = 0; j < LA; ++j) {
       const uint16_t* src = asrc[j] + (int64_t)kk * KS;
@@ -592,7 +598,7 @@ hipError_t launch_gemm(int epi, const GemmPlan& plan, const uint16_t* A, const u
   if (epi == kGemmSwiGLU && N % 32) return hipErrorInvalidValue;  // whole 16-output gate/up blocks
   // the nonlinearity and the residual update need complete sums: only the partial epilogue splits K
   if (epi != kGemmPartialF32 && plan.slices != 1) return hipErrorInvalidValue;
-  const Params p{A, W, W2, M, N, K, plan.slices, C, Cb, err_flag, 0, nullptr};
+  const Params p{A, W, W2, M, N, K, plan.slices, C, Cb, err_flag, 0, nullptr, 1};
   switch (epi) {
     case kGemmResidF32: return launch_tile<kGemmResidF32>(p, plan.tile, s);
     case kGemmSwiGLU: return launch_tile<kGemmSwiGLU>(p, plan.tile, s);
@@ -679,6 +685,28 @@ __global__ __launch_bounds__(256) void head_rows_kernel(const void* in, int in_b
   }
 }
 
+// Order of the logits' K steps, the same in every tile and kernel: equal rows of
+// the matrix then give equal logits wherever they lie (the lowest index of a tie
+// is the caller's to find) and a row the same bits however many rows are asked
+// for.  A stride of a quarter of the steps and one: the loads in flight spread
+// over a row, where all workgroups in natural order press on a few memory
+// channels (8B head, 5 and 64 fp32 rows: 217 and 245 us in natural order, 175
+// and 204 so; 164 and 203 with a start of its own for each tile; strides of 5 to
+// 33 steps of the 64 were no faster than 17).
+static int logits_kstride(int nk) {
+  int s = nk > 4 ? nk / 4 + 1 : 1;
+  auto gcd = [](int a, int b) {
+    while (b) {
+      const int r = a % b;
+      a = b;
+      b = r;
+    }
+    return a;
+  };
+  while (gcd(s, nk) != 1) ++s;
+  return s;
+}
+
 hipError_t launch_head_logits(const void* in, int in_bf16, const uint16_t* gain, const uint16_t* w, int rows, int N,
                               int K, float eps, uint16_t* a, float* row_scale, float* logits, int* err_flag,
                               hipStream_t s) {
@@ -694,7 +722,7 @@ hipError_t launch_head_logits(const void* in, int in_bf16, const uint16_t* gain,
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const int M = 32 * blocks * parts;
-  const Params p{a, w, nullptr, M, N, K, 1, logits, nullptr, err_flag, rows, row_scale};
+  const Params p{a, w, nullptr, M, N, K, 1, logits, nullptr, err_flag, rows, row_scale, logits_kstride(K / BK)};
   const int tile = gemm_plan(epi, M, N, K, 0).tile;
   return parts == 1 ? launch_tile<kGemmLogits>(p, tile, s) : launch_tile<kGemmLogitsSplit>(p, tile, s);
 }

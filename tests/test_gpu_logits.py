@@ -1,0 +1,63 @@
+"""kf_head_logits over more rows than one GEMV pass takes (the matrix-core logits)."""
+import numpy as np
+import pytest
+
+import synth
+from tests.helpers import SeededModel
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch():
+    import torch as t
+    if not t.cuda.is_available():
+        pytest.skip("no GPU")
+    return t
+
+
+@pytest.fixture(scope="module")
+def st():
+    from paper_2609_34045_amd import stage
+    return stage
+
+
+def host(t):
+    return t.float().cpu().numpy().astype(np.float64)
+
+
+def head_stage(st, hidden, vocab, cfg, edit=None):
+    """A stage whose layer is not used, and its head's tensors."""
+    shape = synth.ModelShape(1, hidden, 1, 1, 64, 64, vocab, 1e-5, 1e4)
+    model = SeededModel(shape, cfg)
+    head = {k: np.array(v, copy=True) for k, v in model.head().items()}
+    if edit:
+        edit(head)
+    return shape, head, st.Stage(shape, 0, 1, model.layer, head)
+
+
+@pytest.mark.parametrize("io", ["float32", "bfloat16"])
+@pytest.mark.parametrize("hidden,vocab", [(320, 777), (512, 40003)])
+def test_equal_rows_give_equal_logits(torch, st, hidden, vocab, io):
+    """Equal LM-head rows in different column tiles give exactly equal logits (the lowest index then wins an argmax),
+    equal hidden rows in different row tiles equal rows, and a row the same bits in a call of 5 rows as in one of
+    600 (several chunks): every element sums its products in one order whatever tile it lies in."""
+    cols = [3, 130, 300, 511, 512, 770] + ([9000, vocab - 1] if vocab > 9000 else [])
+
+    def twins(head):
+        head["lm_head"][cols] = head["lm_head"][3]
+
+    shape, _, g = head_stage(st, hidden, vocab, 82, twins)
+    x = synth.hidden_states(82, synth.STREAM_DECODE_HIDDEN, 0, 600, hidden)
+    same = [1, 4, 33, 63, 70, 140, 255, 256, 399, 599]
+    x[same] = x[1]
+    x = torch.from_numpy(x).to(getattr(torch, io)).cuda()
+    whole = g.head_logits(x)
+    for rows in (5, 33, 64, 65, 97, 128, 129, 200, 256, 300, 600):
+        y = g.head_logits(x[:rows].contiguous())
+        assert torch.equal(y[:, cols], y[:, 3:4].expand(-1, len(cols))), rows
+        r = [i for i in same if i < rows]
+        assert torch.equal(y[r], y[1:2].expand(len(r), -1)), rows
+        assert torch.equal(y, whole[:rows]), rows
+    g.sync()
+    g.close()
