@@ -441,13 +441,16 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_rows_kernel(const Params p)
     const uint16_t* wb = EPI == kGemmSwiGLU && (r & 16) ? p.W2 : p.W;
     wsrc[j] = wb + (int64_t)min(wr, w_rows - 1) * K + chunk(r);  // rows past N repeat the last; never stored
   }
-  // Workgroups of an unsplit launch walk K from starts of their own, wrapping
+  // The column tiles of an unsplit launch walk K from starts of their own, wrapping
   // around, as do those whose slices begin at multiples of 4 KB within a row: all
   // at the same offset of rows a power of two apart, they press on a few memory
   // channels at a time (8B-shaped gate/up over 32 rows: 50.9 -> 40.7 us, with the
-  // weights loaded non-temporally; 64 rows 53.3 -> 44.2).  Logits keep one order
-  // in every tile (logits_kstride).
-  const int rot = !is_logits(EPI) && (p.splitk == 1 || (nk * RB) % 4096 == 0) ? (int)(((unsigned)t * 13u) % (unsigned)nk) : 0;
+  // weights loaded non-temporally; 64 rows 53.3 -> 44.2).  Row tiles of one column
+  // tile share its start: they read the same weights at the same time, and every
+  // row is summed in the same order.  Logits keep one order in every tile
+  // (logits_kstride).
+  const bool rotate = !is_logits(EPI) && (p.splitk == 1 || (nk * RB) % 4096 == 0);
+  const int rot = rotate ? (int)(((unsigned)(t / mt) * 13u) % (unsigned)nk) : 0;
   auto issue = [&](int k) {
     uint8_t* st = smem + (k % D) * STAGE;
     const int kk = is_logits(EPI) ? (int)((unsigned)(k * p.kstride) % (unsigned)nk) : k + rot < nk ? k + rot : k + rot - nk;
