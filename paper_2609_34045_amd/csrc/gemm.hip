@@ -89,7 +89,7 @@ struct Params {
   uint16_t* Cb;
   int* err_flag;
   int rows_out;            // logits: rows of the output (M counts the rows of A)
-  const float* row_scale;  // logits: factor of each output row
+  const float2* row_scale;  // logits: the two factors of each output row
   int kstride;             // logits: K steps are taken in the order 0, kstride, 2 kstride, .. (mod their number)
 };
 
@@ -149,12 +149,12 @@ __device__ __forceinline__ void store_tile(const Params& p, const f32x16 (&acc)[
       for (int v = 0; v < 16; ++v) {
         const int row = row0 + 32 * i + 8 * (v >> 2) + rq + (v & 3);
         if (row >= p.rows_out) continue;
-        const float scale = p.row_scale[row];
+        const float2 scale = p.row_scale[row];
 #pragma unroll
         for (int j = 0; j < JW; ++j) {
           const int col = n0 + 32 * (bw0 + j) + rl;
           if (col >= p.N) continue;
-          const float y = acc[i][j][v] * scale;
+          const float y = acc[i][j][v] * scale.x * scale.y;
           nan |= y != y;
           p.C[(int64_t)row * p.N + col] = y;
         }
@@ -619,11 +619,11 @@ hipError_t launch_gemm(int epi, const GemmPlan& plan, const uint16_t* A, const u
 // largest value; a bf16 row without a gain is its high part.  The products
 // and their sums are then those of fp32 rows with fp16 weights (error against
 // 64-bit sums, 8B head, 256 rows: 2.0e-4 of the logits before and after, the
-// rounding of the weights).  Row r's factor is 1 / rms(v) and the power of two
-// taken back.  One workgroup per row; rows past `rows` fill their block with zeros.
+// rounding of the weights).  Row r's factors are 1 / rms(v) and the power of two
+// back (one product of both could leave fp32's range).  One workgroup per row; rows past `rows` fill their block with zeros.
 template <int PARTS>
 __global__ __launch_bounds__(256) void head_rows_kernel(const void* in, int in_bf16, const uint16_t* gain, int rows,
-                                                        int H, float eps, uint16_t* a, float* row_scale) {
+                                                        int H, float eps, uint16_t* a, float2* row_scale) {
   const int r = blockIdx.x, tid = threadIdx.x;
   uint2* hi = reinterpret_cast<uint2*>(a + (int64_t)(PARTS * (r & ~31) + (r & 31)) * H);
   uint2* lo = reinterpret_cast<uint2*>(a + (int64_t)(PARTS * (r & ~31) + 32 + (r & 31)) * H);
@@ -669,10 +669,12 @@ __global__ __launch_bounds__(256) void head_rows_kernel(const void* in, int in_b
   __syncthreads();
   ss = (rs[0] + rs[1]) + (rs[2] + rs[3]);
   mx = fmaxf(fmaxf(rm[0], rm[1]), fmaxf(rm[2], rm[3]));
-  // a row of zeros or with an infinity keeps its scale (its logits are NaN or
-  // 0 through the factor, as products of the row itself would be)
-  const int e = mx > 0.f && mx < INFINITY ? 13 - ilogbf(mx) : 0;
-  if (tid == 0) row_scale[r] = ldexpf(1.0f / sqrtf(ss / (float)H + eps), -e);
+  // 2^e brings the row below 2^14; a row of zeros stays as it is.  Beside an infinity (a
+  // value, or its product with the gain) the finite values are brought there from the
+  // largest fp32 can hold, and 2^-140, the factor back from 2^e at the other end, is one
+  // fp32 holds (rows below it keep their last bit, 2^-149, above fp16's).
+  const int e = mx == 0.f ? 0 : mx < INFINITY ? min(13 - ilogbf(mx), 140) : 13 - 127;
+  if (tid == 0) row_scale[r] = float2{1.0f / sqrtf(ss / (float)H + eps), ldexpf(1.0f, -e)};
   for (int k = tid; k < H / 4; k += 256) {
     const f32x4 w = gained(load(k), k);
     uint16_t h[4], l[4];
@@ -681,7 +683,7 @@ __global__ __launch_bounds__(256) void head_rows_kernel(const void* in, int in_b
       const float v = ldexpf(w[i], e);
       const _Float16 vh = (_Float16)v;
       h[i] = __builtin_bit_cast(uint16_t, vh);
-      l[i] = __builtin_bit_cast(uint16_t, (_Float16)(v - (float)vh));
+      l[i] = __builtin_bit_cast(uint16_t, (_Float16)(fabsf(v) < INFINITY ? v - (float)vh : 0.f));
     }
     hi[k] = uint2{h[0] | ((uint32_t)h[1] << 16), h[2] | ((uint32_t)h[3] << 16)};
     if (PARTS == 2) lo[k] = uint2{l[0] | ((uint32_t)l[1] << 16), l[2] | ((uint32_t)l[3] << 16)};
@@ -711,7 +713,7 @@ static int logits_kstride(int nk) {
 }
 
 hipError_t launch_head_logits(const void* in, int in_bf16, const uint16_t* gain, const uint16_t* w, int rows, int N,
-                              int K, float eps, uint16_t* a, float* row_scale, float* logits, int* err_flag,
+                              int K, float eps, uint16_t* a, float2* row_scale, float* logits, int* err_flag,
                               hipStream_t s) {
   const int parts = in_bf16 && !gain ? 1 : 2;
   if (rows <= 0 || rows > kHeadChunk * 2 / parts || N <= 0 || K <= 0 || K % BK) return hipErrorInvalidValue;

@@ -130,7 +130,7 @@ struct kf_stage {
   float* part_val = nullptr;
   int* part_idx = nullptr;
   uint16_t* head_a = nullptr;     // logits of many rows: a chunk's rows as matrix operands
-  float* head_scale = nullptr;    // and the factor of each of its rows
+  float2* head_scale = nullptr;   // and the factors of each of its rows
   int lm_wg = 0;       // capacity of the argmax partials per batch row
   int lm_wg_used = 0;  // partials per row written by the last LM-head launch
   int kept_rows = 0;   // rows the last decode kept for the head (called without hidden output), else 0
@@ -312,7 +312,7 @@ static int64_t decode_ws_bytes(const kf_model_config& c, int has_head) {
   if (has_head) {
     const int64_t wgs = (c.vocab + 3) / 4;  // enough for any rows-per-workgroup choice
     n += 2 * align256(B * wgs * 4);
-    n += align256(2 * kHeadChunk * H * 2) + align256(2 * kHeadChunk * 4);  // head_a, head_scale
+    n += align256(2 * kHeadChunk * H * 2) + align256(2 * kHeadChunk * 8);  // head_a, head_scale
   }
   n += 256;  // error flag
   return n;
@@ -519,7 +519,7 @@ kf_status kf_stage_init(const kf_model_config* cfg, int32_t lo, int32_t hi, int3
     s->part_val = (float*)take(B * s->lm_wg * 4);
     s->part_idx = (int*)take(B * s->lm_wg * 4);
     s->head_a = (uint16_t*)take((int64_t)2 * kHeadChunk * H * 2);
-    s->head_scale = (float*)take(2 * kHeadChunk * 4);
+    s->head_scale = (float2*)take(2 * kHeadChunk * 8);
   }
   s->err_flag = (int*)take(4);
 

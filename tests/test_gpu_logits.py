@@ -61,3 +61,28 @@ def test_equal_rows_give_equal_logits(torch, st, hidden, vocab, io):
         assert torch.equal(y, whole[:rows]), rows
     g.sync()
     g.close()
+
+
+def test_rows_of_extreme_magnitude(torch, st):
+    """Rows near and below the smallest normal fp32 values, against 64-bit sums over the matrix as stored (1e-5 of the
+    largest logit: fp32's own spacing there is 1e-7), and a row with one product of value and gain beyond fp32, which
+    gives infinities as the GEMV of up to four rows does."""
+    def edit(head):
+        head["final_norm"][7] = 0x7149  # 1e30 in bf16: the gain stays out of the matrix
+
+    shape, head, g = head_stage(st, 320, 777, 84, edit)
+    x = synth.hidden_states(84, synth.STREAM_DECODE_HIDDEN, 0, 40, 320)
+    x[:, 7] = 0
+    x[5] *= 1e-38
+    x[6] *= 1e-40
+    x[9, 7], x[10, 7] = 1e10, -1e10
+    gain, w = ((head[k].astype(np.uint32) << 16).view(np.float32) for k in ("final_norm", "lm_head"))
+    ref = (x[5:7] * gain.astype(np.float64) / np.sqrt(shape.rms_eps)) @ w.astype(np.float16).astype(np.float64).T
+    x = torch.from_numpy(x).cuda()
+    whole = host(g.head_logits(x))
+    parts = host(g.head_logits(x[8:12].contiguous()))
+    assert np.isinf(parts[1:3]).all() and np.array_equal(whole[9:11], parts[1:3])
+    for r in (0, 1):
+        assert np.max(np.abs(whole[5 + r] - ref[r])) <= 1e-5 * np.max(np.abs(ref[r])), r
+    g.sync()
+    g.close()
