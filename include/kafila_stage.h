@@ -123,7 +123,8 @@ const char* kf_last_error(void);
  *                held: fp16 matrices, bf16 gains; both gains included)
  *   beta_head  : bytes of the head's weights (embedding + final gain + LM head), 0 without the head
  *   resident   : device bytes kf_stage_init + kf_kv_create(max_users, max_ctx) would hold for
- *                layers [lo, hi): weights, KV cache, RoPE table and decode workspaces
+ *                layers [lo, hi): weights, KV cache, RoPE table and decode workspaces (not the
+ *                workspaces that a first prefill or many-row logits call allocates)
  * Host only; any output pointer may be NULL.  KF_EINVAL for an invalid config or range.
  */
 kf_status kf_stage_bytes(const kf_model_config* cfg, int32_t layer_lo, int32_t layer_hi, int32_t has_head,
@@ -318,7 +319,10 @@ kf_status kf_stage_prefill_noalloc(kf_stage* stage, kf_kv* kv, int32_t user, int
  * [rows, H] in dtype (KF_F32 or KF_BF16), any rows >= 1.  Head stages only (else KF_ESTATE).
  * Equal LM-head rows give exactly equal logits.  Up to four rows and more rows sum in
  * different orders (the last bits of a row's logits may differ between the two); among
- * calls of more than four, a row's logits have the same bits whatever the count.
+ * calls of more than four, a row's logits have the same bits whatever the count.  These
+ * use a workspace of 1 KB per hidden value, allocated at a stage's first such call and kept;
+ * where it cannot be had (no device memory left, or that call is under HIP graph capture)
+ * the rows go four at a time, in the order and at the cost of such calls.
  * hidden_dev NULL: the rows the stage's last kf_stage_decode kept (its hidden_out_dev
  * was NULL); rows must equal that decode's batch and dtype is ignored (else KF_ESTATE,
  * also when the last decode returned its rows or failed).

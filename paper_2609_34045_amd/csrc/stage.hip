@@ -129,7 +129,8 @@ struct kf_stage {
   float* kraw = nullptr;  // [B][nkv][hd] new keys before their norm and RoPE (qk_norm blocks)
   float* part_val = nullptr;
   int* part_idx = nullptr;
-  uint16_t* head_a = nullptr;     // logits of many rows: a chunk's rows as matrix operands
+  // logits of many rows (head_reserve): a chunk's rows as matrix operands
+  uint16_t* head_a = nullptr;
   float2* head_scale = nullptr;   // and the factors of each of its rows
   int lm_wg = 0;       // capacity of the argmax partials per batch row
   int lm_wg_used = 0;  // partials per row written by the last LM-head launch
@@ -312,7 +313,6 @@ static int64_t decode_ws_bytes(const kf_model_config& c, int has_head) {
   if (has_head) {
     const int64_t wgs = (c.vocab + 3) / 4;  // enough for any rows-per-workgroup choice
     n += 2 * align256(B * wgs * 4);
-    n += align256(2 * kHeadChunk * H * 2) + align256(2 * kHeadChunk * 8);  // head_a, head_scale
   }
   n += 256;  // error flag
   return n;
@@ -518,8 +518,6 @@ kf_status kf_stage_init(const kf_model_config* cfg, int32_t lo, int32_t hi, int3
     s->lm_wg = (int)((V + kGemvRows - 1) / kGemvRows);  // the 8-row grid, the larger of the LM head's two
     s->part_val = (float*)take(B * s->lm_wg * 4);
     s->part_idx = (int*)take(B * s->lm_wg * 4);
-    s->head_a = (uint16_t*)take((int64_t)2 * kHeadChunk * H * 2);
-    s->head_scale = (float2*)take(2 * kHeadChunk * 8);
   }
   s->err_flag = (int*)take(4);
 
@@ -584,6 +582,7 @@ kf_status kf_stage_destroy(kf_stage* s) {
   hipStreamSynchronize(s->stream);
   if (s->arena) hipFree(s->arena);
   if (s->ws) hipFree(s->ws);
+  if (s->head_a) hipFree(s->head_a);
   prefill_free(s->pf);
   for (hipEvent_t e : s->ev) hipEventDestroy(e);
   delete s;
@@ -1132,6 +1131,32 @@ static kf_status head_launch(kf_stage* s, int rows, const void* hidden, kf_dtype
   return KF_OK;
 }
 
+// The many-row logits' workspace, 1 KB a hidden value, from a stage's first such
+// call to its end (like the prefill's it is not part of `resident`).  False
+// where it cannot be had: no device memory left, or the stream is being captured.
+static bool head_reserve(kf_stage* s) {
+  if (s->head_a) return true;
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s->stream, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone) {
+    (void)hipGetLastError();
+    return false;
+  }
+  const int64_t rows = 2 * kHeadChunk, a = align256(rows * s->cfg.hidden * 2);
+  char* mem = nullptr;
+  // Relaxed: the allocation leaves captures of other threads alone.
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  (void)hipThreadExchangeStreamCaptureMode(&mode);
+  const hipError_t e = hipMalloc((void**)&mem, a + rows * sizeof(float2));
+  (void)hipThreadExchangeStreamCaptureMode(&mode);
+  if (e != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  s->head_a = (uint16_t*)mem;
+  s->head_scale = (float2*)(mem + a);
+  return true;
+}
+
 kf_status kf_head_logits(kf_stage* s, int32_t rows, const void* hidden, kf_dtype dtype, float* logits) {
   kf_status st = head_common(s, rows, hidden, dtype);
   if (st != KF_OK) return st;
@@ -1143,14 +1168,23 @@ kf_status kf_head_logits(kf_stage* s, int32_t rows, const void* hidden, kf_dtype
   // passes of the GEMV before, 470 -> 168 us, about one pass).
   const kf_model_config& c = s->cfg;
   const bool bf16 = dtype == KF_BF16;
+  const size_t row_bytes = (size_t)c.hidden * (bf16 ? 2 : 4);
+  if (!head_reserve(s)) {  // four rows at a time
+    for (int r0 = 0; r0 < rows; r0 += kMaxBatch) {
+      st = head_launch(s, rows - r0 < kMaxBatch ? rows - r0 : kMaxBatch, (const char*)hidden + r0 * row_bytes, dtype,
+                       logits + (size_t)r0 * c.vocab);
+      if (st != KF_OK) return st;
+    }
+    return KF_OK;
+  }
   const uint16_t* gain = s->head_fold ? nullptr : s->g_final;
   const int chunk = bf16 && !gain ? 2 * kHeadChunk : kHeadChunk;
   const Tracer tr = s->tracer();
   for (int r0 = 0; r0 < rows; r0 += chunk) {
     const int n = rows - r0 < chunk ? rows - r0 : chunk;
     tr.begin(KF_K_LMHEAD);
-    const hipError_t e = launch_head_logits((const char*)hidden + (size_t)r0 * c.hidden * (bf16 ? 2 : 4), bf16, gain,
-                                            s->lm_head, n, c.vocab, c.hidden, c.rms_eps, s->head_a, s->head_scale,
+    const hipError_t e = launch_head_logits((const char*)hidden + r0 * row_bytes, bf16, gain, s->lm_head, n, c.vocab,
+                                            c.hidden, c.rms_eps, s->head_a, s->head_scale,
                                             logits + (size_t)r0 * c.vocab, s->err_flag, s->stream);
     tr.end(KF_K_LMHEAD);
     KF_HIP(e, "logits launch");

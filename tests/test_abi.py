@@ -78,6 +78,17 @@ def test_stage_bytes_matches_shape_arithmetic():
     assert stage.stage_bytes(synth.SHAPE_32B, 16, 32, False, 1, 4160)[0] == 975_196_160
 
 
+@pytest.mark.parametrize("name", ["SHAPE_TINY", "SHAPE_8B", "SHAPE_70B"])
+def test_head_adds_its_tensors_and_argmax_partials(name):
+    """The head's share of the resident bytes: its three tensors and the argmax partials of four rows (a value and an
+    index per four vocabulary rows), so that a placement at the edge of its budget is admitted as it always was."""
+    from paper_2609_34045_amd import stage
+    s = getattr(synth, name)
+    up = lambda n: (n + 255) // 256 * 256  # noqa: E731
+    bare, head = (stage.stage_bytes(s, 0, 1, h, 1, 2048) for h in (False, True))
+    assert head[2] - bare[2] == head[1] + 2 * up(4 * ((s.vocab + 3) // 4) * 4)
+
+
 def _cfg(**kw):
     from paper_2609_34045_amd import stage
     base = dict(n_layers=4, hidden=512, n_q_heads=8, n_kv_heads=2, head_dim=64, ffn=1408, vocab=100,

@@ -86,3 +86,40 @@ def test_rows_of_extreme_magnitude(torch, st):
         assert np.max(np.abs(whole[5 + r] - ref[r])) <= 1e-5 * np.max(np.abs(ref[r])), r
     g.sync()
     g.close()
+
+
+def test_first_call_under_capture(torch, st):
+    """Nine rows as a stage's first call of more than four, while its stream is being captured: four at a time, without
+    the workspace; after an eager call a capture takes the many-row path.  Both graphs replayed among eager work."""
+    shape, head, g = head_stage(st, 320, 777, 85)
+    x = torch.from_numpy(synth.hidden_states(85, synth.STREAM_DECODE_HIDDEN, 0, 9, 320)).cuda()
+    fours = torch.cat([g.head_logits(x[r:r + 4].contiguous()) for r in range(0, 9, 4)])
+    main, side = torch.cuda.current_stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+
+    def captured():
+        graph, y = torch.cuda.CUDAGraph(), torch.empty(9, 777, device="cuda")
+        g.set_stream(side)
+        with torch.cuda.graph(graph, stream=side):
+            g.head_logits(x, out=y)
+        g.set_stream(main)
+        return graph, y
+
+    def check(graph, y, want):
+        for _ in range(3):
+            y.zero_()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(y, want)
+            g.head_logits(x[:4].contiguous())
+            torch.cuda.synchronize()
+
+    first = captured()
+    check(*first, fours)
+    many = g.head_logits(x)
+    torch.cuda.synchronize()
+    second = captured()
+    check(*second, many)
+    check(*first, fours)
+    g.sync()
+    g.close()
