@@ -89,8 +89,9 @@ struct Params {
   uint16_t* Cb;
   int* err_flag;
   int rows_out;            // logits: rows of the output (M counts the rows of A)
-  const float2* row_scale;  // logits: the two factors of each output row
+  const double* row_scale;  // logits: the factor of each output row
   int kstride;             // logits: K steps are taken in the order 0, kstride, 2 kstride, .. (mod their number)
+  int fold;                // logits: K steps that an accumulator runs over (Accum)
 };
 
 // Rows of A per output row: the logits of fp32 rows take each row as two fp16
@@ -98,6 +99,41 @@ struct Params {
 // parts, that add into one accumulator.
 constexpr int parts_of(int epi) { return epi == kGemmLogitsSplit ? 2 : 1; }
 constexpr bool is_logits(int epi) { return epi == kGemmLogits || epi == kGemmLogitsSplit; }
+
+// Accumulators of a wave's MB x JW output blocks.
+template <int EPI, int MB, int JW>
+struct Accum {
+  f32x16 acc[MB][JW] = {};
+  __device__ __forceinline__ void begin_step(int, const Params&) {}
+};
+
+// Those of the logits.  A matrix instruction rounds into its accumulator twice, so
+// one chain of them over all of K loses what the fp32 tree sums of a GEMV keep: against
+// 64-bit sums over the stored matrix, K = 4096, fp32 rows 5.8e-7 (GEMV 1.2e-7),
+// bf16 rows 4.2e-7 (1.0e-7).  An accumulator therefore runs over p.fold steps and is
+// then added into `sum`, keeping what that sum rounded off.
+template <int MB, int JW>
+struct LogitAccum {
+  f32x16 acc[MB][JW] = {}, sum[MB][JW] = {};
+  __device__ __forceinline__ void begin_step(int k, const Params& p) {
+    if (k % p.fold) return;
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+      for (int j = 0; j < JW; ++j)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          const float s = sum[i][j][v], a = acc[i][j][v], t = s + a;
+          // beside an infinite sum the rest is no number; any finite one will do
+          acc[i][j][v] = __builtin_amdgcn_fmed3f(a - (t - s), -1e38f, 1e38f);
+          sum[i][j][v] = t;
+        }
+  }
+};
+template <int MB, int JW>
+struct Accum<kGemmLogits, MB, JW> : LogitAccum<MB, JW> {};
+template <int MB, int JW>
+struct Accum<kGemmLogitsSplit, MB, JW> : LogitAccum<MB, JW> {};
 
 // Large tiles: TM rows (256 or 128) x 32 NB columns, eight waves (two per SIMD).
 // LDS ring depths: activation loads run up to ring_a K steps ahead, weight
@@ -114,8 +150,9 @@ constexpr int w_stage(int NB) { return 32 * NB * ROW_BYTES; }
 // times JW 32-column blocks from block bw0 of the tile at column n0.  Lane l
 // holds column l % 32 of each block.
 template <int EPI, int MB, int JW>
-__device__ __forceinline__ void store_tile(const Params& p, const f32x16 (&acc)[MB][JW], int lane, int row0, int n0,
+__device__ __forceinline__ void store_tile(const Params& p, const Accum<EPI, MB, JW>& sums, int lane, int row0, int n0,
                                            int bw0, int ks) {
+  const auto& acc = sums.acc;
   const int rl = lane & 31, rq = 4 * (lane >> 5);
   if (EPI == kGemmSwiGLU) {
     // Each 32-column block holds 16 outputs: columns 0-15 their gate rows,
@@ -141,7 +178,7 @@ __device__ __forceinline__ void store_tile(const Params& p, const f32x16 (&acc)[
         }
       }
     raise_err(p.err_flag, bad, kErrF16Range);
-  } else if (is_logits(EPI)) {
+  } else if constexpr (is_logits(EPI)) {
     bool nan = false;
 #pragma unroll
     for (int i = 0; i < MB; ++i)
@@ -149,12 +186,12 @@ __device__ __forceinline__ void store_tile(const Params& p, const f32x16 (&acc)[
       for (int v = 0; v < 16; ++v) {
         const int row = row0 + 32 * i + 8 * (v >> 2) + rq + (v & 3);
         if (row >= p.rows_out) continue;
-        const float2 scale = p.row_scale[row];
+        const double scale = p.row_scale[row];
 #pragma unroll
         for (int j = 0; j < JW; ++j) {
           const int col = n0 + 32 * (bw0 + j) + rl;
           if (col >= p.N) continue;
-          const float y = acc[i][j][v] * scale.x * scale.y;
+          const float y = (float)(((double)sums.sum[i][j][v] + (double)acc[i][j][v]) * scale);
           nan |= y != y;
           p.C[(int64_t)row * p.N + col] = y;
         }
@@ -212,13 +249,8 @@ __device__ __forceinline__ void gemm_wave(const Params& p, uint8_t* smem, const 
     __builtin_amdgcn_global_load_lds(src, (lds_ptr)dst, 16, 0, 0);
   };
 
-  f32x16 acc[MB / PA][JW];
-#pragma unroll
-  for (int i = 0; i < MB / PA; ++i)
-#pragma unroll
-    for (int j = 0; j < JW; ++j)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+  Accum<EPI, MB / PA, JW> sums;
+  auto& acc = sums.acc;
 
   // The K loop is scheduled by hand: each slice is SLOTS MFMA slots; the
   // first slots also issue the fragment reads for the next slice (and, in the
@@ -275,6 +307,7 @@ __device__ __forceinline__ void gemm_wave(const Params& p, uint8_t* smem, const 
   for (int q = 0; q < RD; ++q) read_frag(0, 0, q, fa[0], fw[0]);
   static_assert(SS % 2 == 0, "a step starts with its fragments in buffer 0");
   for (int k = 0; k + 1 < nk; ++k) {
+    sums.begin_step(k, p);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int s = 0; s + 1 < SS; ++s)
@@ -292,6 +325,7 @@ __device__ __forceinline__ void gemm_wave(const Params& p, uint8_t* smem, const 
   }
   {
     const int k = nk - 1;
+    sums.begin_step(k, p);
 #pragma unroll
     for (int s = 0; s + 1 < SS; ++s)
       half(fa[s & 1], fw[s & 1], k, s + 1, fa[(s + 1) & 1], fw[(s + 1) & 1], false, 0, 0);
@@ -301,7 +335,7 @@ __device__ __forceinline__ void gemm_wave(const Params& p, uint8_t* smem, const 
   }
   wait_vm<0>();  // no load may still be writing LDS when the workgroup ends
 
-  store_tile<EPI, MB / PA, JW>(p, acc, lane, (m0 + am0) / PA, n0, bw0, ks);
+  store_tile<EPI, MB / PA, JW>(p, sums, lane, (m0 + am0) / PA, n0, bw0, ks);
 }
 
 // Tiles of TM rows x 32 NB columns (narrower or lower ones where they fill the
@@ -470,13 +504,8 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_rows_kernel(const Params p)
 
   constexpr int PA = parts_of(EPI);  // A blocks per accumulator block
   static_assert(MBW % PA == 0, "whole output blocks");
-  f32x16 acc[MBW / PA][JW];
-#pragma unroll
-  for (int i = 0; i < MBW / PA; ++i)
-#pragma unroll
-    for (int j = 0; j < JW; ++j)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+  Accum<EPI, MBW / PA, JW> sums;
+  auto& acc = sums.acc;
 
   const int wm = wave / WN, wn = wave % WN;
   const int rl = lane & 31, kh = lane >> 5;
@@ -503,6 +532,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_rows_kernel(const Params p)
     block_barrier();
     if (k + D - 1 < nk) issue(k + D - 1);
     const uint8_t* st = smem + (k % D) * STAGE;
+    sums.begin_step(k, p);
 #pragma unroll
     for (int s = 0; s < KS / 16; ++s) {
       const int c = ((2 * s + kh) ^ f) * 16;
@@ -518,7 +548,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_rows_kernel(const Params p)
     }
     wait_lds();  // no read of this step's stage is in flight past the next barrier
   }
-  store_tile<EPI, MBW / PA, JW>(p, acc, lane, (m0 + 32 * MBW * wm) / PA, n0, JW * wn, ks);
+  store_tile<EPI, MBW / PA, JW>(p, sums, lane, (m0 + 32 * MBW * wm) / PA, n0, JW * wn, ks);
 }
 
 }  // namespace
@@ -539,6 +569,12 @@ static constexpr Tile kTiles[] = {
 };
 constexpr int kTileCount = sizeof(kTiles) / sizeof(kTiles[0]);
 
+// Tiles built for an epilogue: the logits' two sets of sums leave no registers for one
+// part of 256 x 160 and wider, and two parts of a row take two 32-row blocks of a wave.
+constexpr bool has_tile(int epi, int t) {
+  return epi == kGemmLogits ? t <= 5 : epi == kGemmLogitsSplit ? t >= 1 : true;
+}
+
 // The tile and K slices of least estimated time: whole rounds of the 256 CUs
 // times a slice's K steps, 4 us for the launch, its first loads and its
 // stores, and for each slice 8 bytes per value (a split product's slices are
@@ -556,11 +592,13 @@ GemmPlan gemm_plan(int epi, int M, int N, int K, int64_t part_elems) {
     const Tile& T = kTiles[t];
     if (T.few && M > 128) continue;
     if (T.rows == 128 && !T.few && M <= 128) continue;  // the few-row tile of this size streams better (108 against 116 us)
-    if (t == 0 && epi == kGemmLogitsSplit) continue;  // its waves hold one 32-row block
+    if (!has_tile(epi, t)) continue;
     const int64_t tiles = (int64_t)((M + T.rows - 1) / T.rows) * ((N + T.cols - 1) / T.cols);
     for (int s = 1; s <= kGemmMaxSlices; ++s) {
       if (s > 1 && (s > nk / 4 || epi != kGemmPartialF32 || (int64_t)s * M * N > part_elems)) break;
-      const float us = (float)((tiles * s + 255) / 256) * ((nk + s - 1) / s) * T.step_us + 4.f +
+      // 64 one-part accumulators a thread to fold (64 bf16 rows of the 8B head: 232 us, against 204 in tiles of 64 x 128)
+      const float step_us = t == 3 && epi == kGemmLogits ? 1.2f * T.step_us : T.step_us;
+      const float us = (float)((tiles * s + 255) / 256) * ((nk + s - 1) / s) * step_us + 4.f +
                        s * (float)M * N * 8e-6f / 5.f;
       if (best_us == 0.f || us < best_us) {
         best_us = us;
@@ -573,23 +611,27 @@ GemmPlan gemm_plan(int epi, int M, int N, int K, int64_t part_elems) {
 
 template <int EPI>
 static hipError_t launch_tile(const Params& p, int tile, hipStream_t s) {
+  if (tile < 0 || tile >= kTileCount || !has_tile(EPI, tile)) return hipErrorInvalidValue;
   const Tile& T = kTiles[tile];
   const dim3 grid((unsigned)((int64_t)((p.M + T.rows - 1) / T.rows) * ((p.N + T.cols - 1) / T.cols) * p.splitk));
   switch (tile) {
     case 0:
-      if constexpr (parts_of(EPI) == 1)
-        hipLaunchKernelGGL((gemm_rows_kernel<EPI, 1, 1, 1, 4, 4>), grid, dim3(256), 0, s, p);
-      else
-        return hipErrorInvalidValue;
+      if constexpr (has_tile(EPI, 0)) hipLaunchKernelGGL((gemm_rows_kernel<EPI, 1, 1, 1, 4, 4>), grid, dim3(256), 0, s, p);
       break;
     case 1: hipLaunchKernelGGL((gemm_rows_kernel<EPI, 2, 1, 1, 4, 3>), grid, dim3(256), 0, s, p); break;
     case 2: hipLaunchKernelGGL((gemm_rows_kernel<EPI, 2, 1, 2, 4, 4>), grid, dim3(512), 0, s, p); break;
     case 3: hipLaunchKernelGGL((gemm_rows_kernel<EPI, 2, 2, 2, 4, 3>), grid, dim3(512), 0, s, p); break;
     case 4: hipLaunchKernelGGL((gemm_tile_kernel<EPI, 128, 8>), grid, dim3(64 * NW), 0, s, p); break;
     case 5: hipLaunchKernelGGL((gemm_tile_kernel<EPI, 256, 4>), grid, dim3(64 * NW), 0, s, p); break;
-    case 6: hipLaunchKernelGGL((gemm_tile_kernel<EPI, 256, 5>), grid, dim3(64 * NW), 0, s, p); break;
-    case 7: hipLaunchKernelGGL((gemm_tile_kernel<EPI, 256, 7>), grid, dim3(64 * NW), 0, s, p); break;
-    case 8: hipLaunchKernelGGL((gemm_tile_kernel<EPI, 256, 8>), grid, dim3(64 * NW), 0, s, p); break;
+    case 6:
+      if constexpr (has_tile(EPI, 6)) hipLaunchKernelGGL((gemm_tile_kernel<EPI, 256, 5>), grid, dim3(64 * NW), 0, s, p);
+      break;
+    case 7:
+      if constexpr (has_tile(EPI, 7)) hipLaunchKernelGGL((gemm_tile_kernel<EPI, 256, 7>), grid, dim3(64 * NW), 0, s, p);
+      break;
+    case 8:
+      if constexpr (has_tile(EPI, 8)) hipLaunchKernelGGL((gemm_tile_kernel<EPI, 256, 8>), grid, dim3(64 * NW), 0, s, p);
+      break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
@@ -601,7 +643,7 @@ hipError_t launch_gemm(int epi, const GemmPlan& plan, const uint16_t* A, const u
   if (epi == kGemmSwiGLU && N % 32) return hipErrorInvalidValue;  // whole 16-output gate/up blocks
   // the nonlinearity and the residual update need complete sums: only the partial epilogue splits K
   if (epi != kGemmPartialF32 && plan.slices != 1) return hipErrorInvalidValue;
-  const Params p{A, W, W2, M, N, K, plan.slices, C, Cb, err_flag, 0, nullptr, 1};
+  const Params p{A, W, W2, M, N, K, plan.slices, C, Cb, err_flag, 0, nullptr, 1, 1};
   switch (epi) {
     case kGemmResidF32: return launch_tile<kGemmResidF32>(p, plan.tile, s);
     case kGemmSwiGLU: return launch_tile<kGemmSwiGLU>(p, plan.tile, s);
@@ -619,11 +661,12 @@ hipError_t launch_gemm(int epi, const GemmPlan& plan, const uint16_t* A, const u
 // largest value; a bf16 row without a gain is its high part.  The products
 // and their sums are then those of fp32 rows with fp16 weights (error against
 // 64-bit sums, 8B head, 256 rows: 2.0e-4 of the logits before and after, the
-// rounding of the weights).  Row r's factors are 1 / rms(v) and the power of two
-// back (one product of both could leave fp32's range).  One workgroup per row; rows past `rows` fill their block with zeros.
+// rounding of the weights).  Row r's factor is 1 / rms(v) and the power of two back,
+// in 64 bits (fp32 would not hold every such product, and its roundings, the same for a whole row, were
+// half of the logits' error).  One workgroup per row; rows past `rows` fill their block with zeros.
 template <int PARTS>
 __global__ __launch_bounds__(256) void head_rows_kernel(const void* in, int in_bf16, const uint16_t* gain, int rows,
-                                                        int H, float eps, uint16_t* a, float2* row_scale) {
+                                                        int H, float eps, uint16_t* a, double* row_scale) {
   const int r = blockIdx.x, tid = threadIdx.x;
   uint2* hi = reinterpret_cast<uint2*>(a + (int64_t)(PARTS * (r & ~31) + (r & 31)) * H);
   uint2* lo = reinterpret_cast<uint2*>(a + (int64_t)(PARTS * (r & ~31) + 32 + (r & 31)) * H);
@@ -650,18 +693,23 @@ __global__ __launch_bounds__(256) void head_rows_kernel(const void* in, int in_b
     }
     return v;
   };
-  float ss = 0.f, mx = 0.f;
+  double ss = 0.;
+  float mx = 0.f;
   for (int k = tid; k < H / 4; k += 256) {
     const f32x4 v = load(k), w = gained(v, k);
-    ss += (v.x * v.x + v.y * v.y) + (v.z * v.z + v.w * v.w);
-    mx = fmaxf(fmaxf(mx, fmaxf(fabsf(w.x), fabsf(w.y))), fmaxf(fabsf(w.z), fabsf(w.w)));
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      ss = fma((double)v[i], (double)v[i], ss);
+      mx = fmaxf(mx, fabsf(w[i]));
+    }
   }
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) {
     ss += __shfl_xor(ss, o);
     mx = fmaxf(mx, __shfl_xor(mx, o));
   }
-  __shared__ float rs[4], rm[4];
+  __shared__ double rs[4];
+  __shared__ float rm[4];
   if ((tid & 63) == 0) {
     rs[tid >> 6] = ss;
     rm[tid >> 6] = mx;
@@ -671,10 +719,9 @@ __global__ __launch_bounds__(256) void head_rows_kernel(const void* in, int in_b
   mx = fmaxf(fmaxf(rm[0], rm[1]), fmaxf(rm[2], rm[3]));
   // 2^e brings the row below 2^14; a row of zeros stays as it is.  Beside an infinity (a
   // value, or its product with the gain) the finite values are brought there from the
-  // largest fp32 can hold, and 2^-140, the factor back from 2^e at the other end, is one
-  // fp32 holds (rows below it keep their last bit, 2^-149, above fp16's).
-  const int e = mx == 0.f ? 0 : mx < INFINITY ? min(13 - ilogbf(mx), 140) : 13 - 127;
-  if (tid == 0) row_scale[r] = float2{1.0f / sqrtf(ss / (float)H + eps), ldexpf(1.0f, -e)};
+  // largest fp32 can hold.  A sum of squares beyond fp32 makes the factor 0, as the GEMV has it.
+  const int e = mx == 0.f ? 0 : mx < INFINITY ? 13 - ilogbf(mx) : 13 - 127;
+  if (tid == 0) row_scale[r] = (float)ss < INFINITY ? ldexp(1.0 / sqrt(ss / H + (double)eps), -e) : (float)ss == INFINITY ? 0. : (double)NAN;
   for (int k = tid; k < H / 4; k += 256) {
     const f32x4 w = gained(load(k), k);
     uint16_t h[4], l[4];
@@ -712,9 +759,16 @@ static int logits_kstride(int nk) {
   return s;
 }
 
+// K steps that an accumulator of the logits runs over: as many as leave the error of
+// fp32 rows at the GEMV's (K = 4096: 1.2e-7 each, and 1.0e-7 with one step; bf16 rows
+// 0.8e-7 against 1.0e-7).  Each fold costs 4 vector instructions a value: 256 fp32
+// rows of the 8B head 521 us without folds, 570 with one every two steps, 660 with one
+// every step.  A short K affords the latter (K = 320: 1.0e-7 each).
+static int logits_fold(int nk) { return nk < 32 ? 1 : 2; }
+
 hipError_t launch_head_logits(const void* in, int in_bf16, const uint16_t* gain, const uint16_t* w, int rows, int N,
-                              int K, float eps, uint16_t* a, float2* row_scale, float* logits, int* err_flag,
-                              hipStream_t s) {
+                              int K, float eps, uint16_t* a, double* row_scale, float* logits, int* err_flag,
+                              hipStream_t s, int tile) {
   const int parts = in_bf16 && !gain ? 1 : 2;
   if (rows <= 0 || rows > kHeadChunk * 2 / parts || N <= 0 || K <= 0 || K % BK) return hipErrorInvalidValue;
   const int blocks = (rows + 31) / 32, epi = parts == 1 ? kGemmLogits : kGemmLogitsSplit;
@@ -727,8 +781,9 @@ hipError_t launch_head_logits(const void* in, int in_bf16, const uint16_t* gain,
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const int M = 32 * blocks * parts;
-  const Params p{a, w, nullptr, M, N, K, 1, logits, nullptr, err_flag, rows, row_scale, logits_kstride(K / BK)};
-  const int tile = gemm_plan(epi, M, N, K, 0).tile;
+  const Params p{a, w, nullptr, M, N, K, 1, logits, nullptr, err_flag, rows, row_scale, logits_kstride(K / BK),
+                 logits_fold(K / BK)};
+  if (tile < 0) tile = gemm_plan(epi, M, N, K, 0).tile;
   return parts == 1 ? launch_tile<kGemmLogits>(p, tile, s) : launch_tile<kGemmLogitsSplit>(p, tile, s);
 }
 

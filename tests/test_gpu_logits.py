@@ -88,6 +88,26 @@ def test_rows_of_extreme_magnitude(torch, st):
     g.close()
 
 
+@pytest.mark.parametrize("rows,io,limit", [(5, "float32", 1.6e-7), (100, "float32", 1.6e-7), (256, "float32", 1.6e-7),
+                                           (20, "bfloat16", 1.2e-7), (300, "bfloat16", 1.2e-7)])
+def test_sums_as_exact_as_the_gemv(torch, st, rows, io, limit):
+    """4096 products a logit, against 64-bit sums over the matrix as stored.  The GEMV of up to four rows is 1.2e-7 (bf16
+    rows 1.0e-7) off in the 2-norm, a few roundings of 2^-24 / sqrt(3); one chain of matrix instructions over all
+    of K 5.8e-7 (4.2e-7), the high parts of fp32 rows alone about 1e-4.  The limits are a third above the GEMV's."""
+    shape, head, g = head_stage(st, 4096, 700, 86)
+    gain, w = ((head[k].astype(np.uint32) << 16).view(np.float32) for k in ("final_norm", "lm_head"))
+    x = torch.from_numpy(synth.hidden_states(86, synth.STREAM_DECODE_HIDDEN, 0, rows, 4096)).to(getattr(torch, io))
+    xd = x.double().numpy()
+    ref = (xd / np.sqrt(np.mean(xd * xd, axis=1, keepdims=True) + shape.rms_eps)) @ (w * gain).astype(np.float16).astype(np.float64).T
+    x = x.cuda()
+    err = lambda y, r: np.linalg.norm(host(y) - r) / np.linalg.norm(r)  # noqa: E731
+    many, gemv = err(g.head_logits(x), ref), err(g.head_logits(x[:4].contiguous()), ref[:4])
+    print(f"{rows} {io} rows: {many:.2e}, four {gemv:.2e}")
+    assert gemv <= limit and many <= limit
+    g.sync()
+    g.close()
+
+
 def test_first_call_under_capture(torch, st):
     """Nine rows as a stage's first call of more than four, while its stream is being captured: four at a time, without
     the workspace; after an eager call a capture takes the many-row path.  Both graphs replayed among eager work."""
