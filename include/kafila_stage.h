@@ -320,7 +320,7 @@ kf_status kf_stage_prefill_noalloc(kf_stage* stage, kf_kv* kv, int32_t user, int
  * Equal LM-head rows give exactly equal logits.  Up to four rows and more rows sum in
  * different orders (the last bits of a row's logits may differ between the two); among
  * calls of more than four, a row's logits have the same bits whatever the count.  These
- * use a workspace of 1 KB per hidden value, allocated at a stage's first such call and kept;
+ * use a workspace of 6 KB and 1 KB per hidden value, allocated at a stage's first such call and kept;
  * where it cannot be had (no device memory left, or that call is under HIP graph capture)
  * the rows go four at a time, in the order and at the cost of such calls.
  * hidden_dev NULL: the rows the stage's last kf_stage_decode kept (its hidden_out_dev

@@ -124,8 +124,7 @@ struct LogitAccum {
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
           const float s = sum[i][j][v], a = acc[i][j][v], t = s + a;
-          // beside an infinite sum the rest is no number; any finite one will do
-          acc[i][j][v] = __builtin_amdgcn_fmed3f(a - (t - s), -1e38f, 1e38f);
+          acc[i][j][v] = a - (t - s);  // (no infinities here: head_wide_rows_kernel takes their rows)
           sum[i][j][v] = t;
         }
   }
@@ -653,50 +652,61 @@ hipError_t launch_gemm(int epi, const GemmPlan& plan, const uint16_t* A, const u
 }
 
 // ------------------------------------------------------------------ logits of many rows
-// The rows of a chunk as matrix operands.  The head's rows are fp32 (or bf16)
-// and stay that exact: each row v (times the gain, where that is not folded
-// into the matrix) is scaled by a power of two that brings its largest value
-// into [2^13, 2^14) and taken as an fp16 high part and the fp16 rounding of
-// what is left, 22 significant bits and never less than 2^-38 of the row's
-// largest value; a bf16 row without a gain is its high part.  The products
-// and their sums are then those of fp32 rows with fp16 weights (error against
-// 64-bit sums, 8B head, 256 rows: 2.0e-4 of the logits before and after, the
-// rounding of the weights).  Row r's factor is 1 / rms(v) and the power of two back,
-// in 64 bits (fp32 would not hold every such product, and its roundings, the same for a whole row, were
-// half of the logits' error).  One workgroup per row; rows past `rows` fill their block with zeros.
-template <int PARTS>
-__global__ __launch_bounds__(256) void head_rows_kernel(const void* in, int in_bf16, const uint16_t* gain, int rows,
-                                                        int H, float eps, uint16_t* a, double* row_scale) {
-  const int r = blockIdx.x, tid = threadIdx.x;
-  uint2* hi = reinterpret_cast<uint2*>(a + (int64_t)(PARTS * (r & ~31) + (r & 31)) * H);
-  uint2* lo = reinterpret_cast<uint2*>(a + (int64_t)(PARTS * (r & ~31) + 32 + (r & 31)) * H);
-  if (r >= rows) {
-    for (int k = tid; k < H / 4; k += 256) {
-      hi[k] = uint2{0u, 0u};
-      if (PARTS == 2) lo[k] = uint2{0u, 0u};
-    }
-    return;
-  }
-  auto load = [&](int k) {  // values 4 k .. + 3 before the gain
-    if (in_bf16) {
-      const uint2 e = reinterpret_cast<const uint2*>(in)[(int64_t)r * (H / 4) + k];
+// The rows of a chunk as matrix operands.  Each row v (times the gain, where that is not
+// folded into the matrix) is scaled by a power of two that brings its largest value
+// into [2^13, 2^14).  A bf16 row without a gain is taken as fp16, exactly.  An fp32
+// row is taken as an fp16 high part and the fp16 rounding of what is left: 22 to 23 bits
+// of its values down to 2^-16 of the largest, and smaller ones to 2^-39 of it.  The
+// error against 64-bit sums over the stored matrix is then that of the GEMV's fp32
+// sums (1.2e-7 each, 8B head).  Rows of which that is not so, because the fp16 part of
+// a bf16 row is not exact, more than an eighth of an fp32 row's values are
+// that small or there is an infinity, are operands of zeros here and go through
+// head_wide_rows_kernel.  Row r's factor is 1 / rms(v) and the power of two back, in 64
+// bits (fp32 would not hold every such product, and its roundings, the same for a whole
+// row, were half of the logits' error).  One workgroup per row; rows past `rows` fill their block with zeros.
+constexpr int kHeld = 1 << 30;  // wide[r] of a row that its parts hold; else its exponent
+
+struct HeadRow {  // a row of the head's input; values 4 k .. + 3, times the gain
+  const void* in;
+  int bf16;
+  const uint16_t* gain;
+  int64_t first;  // the row's first value / 4
+  __device__ __forceinline__ f32x4 load(int k) const {
+    if (bf16) {
+      const uint2 e = reinterpret_cast<const uint2*>(in)[first + k];
       return f32x4{__uint_as_float(e.x << 16), __uint_as_float(e.x & 0xffff0000u), __uint_as_float(e.y << 16),
                    __uint_as_float(e.y & 0xffff0000u)};
     }
-    return reinterpret_cast<const f32x4*>(in)[(int64_t)r * (H / 4) + k];
-  };
-  auto gained = [&](f32x4 v, int k) {
+    return reinterpret_cast<const f32x4*>(in)[first + k];
+  }
+  __device__ __forceinline__ f32x4 gained(f32x4 v, int k) const {
     if (gain) {
       const uint2 g = reinterpret_cast<const uint2*>(gain)[k];
       v *= f32x4{__uint_as_float(g.x << 16), __uint_as_float(g.x & 0xffff0000u), __uint_as_float(g.y << 16),
                  __uint_as_float(g.y & 0xffff0000u)};
     }
     return v;
+  }
+};
+
+template <int PARTS>
+__global__ __launch_bounds__(256) void head_rows_kernel(const void* in, int in_bf16, const uint16_t* gain, int rows,
+                                                        int H, float eps, uint16_t* a, double* row_scale, int* wide) {
+  const int r = blockIdx.x, tid = threadIdx.x;
+  uint2* hi = reinterpret_cast<uint2*>(a + (int64_t)(PARTS * (r & ~31) + (r & 31)) * H);
+  uint2* lo = reinterpret_cast<uint2*>(a + (int64_t)(PARTS * (r & ~31) + 32 + (r & 31)) * H);
+  auto zeros = [&] {
+    for (int k = tid; k < H / 4; k += 256) {
+      hi[k] = uint2{0u, 0u};
+      if (PARTS == 2) lo[k] = uint2{0u, 0u};
+    }
   };
+  if (r >= rows) return zeros();
+  const HeadRow row{in, in_bf16, gain, (int64_t)r * (H / 4)};
   double ss = 0.;
   float mx = 0.f;
   for (int k = tid; k < H / 4; k += 256) {
-    const f32x4 v = load(k), w = gained(v, k);
+    const f32x4 v = row.load(k), w = row.gained(v, k);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       ss = fma((double)v[i], (double)v[i], ss);
@@ -721,20 +731,106 @@ __global__ __launch_bounds__(256) void head_rows_kernel(const void* in, int in_b
   // value, or its product with the gain) the finite values are brought there from the
   // largest fp32 can hold.  A sum of squares beyond fp32 makes the factor 0, as the GEMV has it.
   const int e = mx == 0.f ? 0 : mx < INFINITY ? 13 - ilogbf(mx) : 13 - 127;
-  if (tid == 0) row_scale[r] = (float)ss < INFINITY ? ldexp(1.0 / sqrt(ss / H + (double)eps), -e) : (float)ss == INFINITY ? 0. : (double)NAN;
+  if (tid == 0) {
+    row_scale[r] = (float)ss == INFINITY ? 0. : ldexp(1.0 / sqrt(ss / H + (double)eps), -e);
+    wide[r] = mx == INFINITY ? e : kHeld;
+  }
+  if (mx == INFINITY) return zeros();
+  int lost = 0;  // values that the parts hold to fewer bits
   for (int k = tid; k < H / 4; k += 256) {
-    const f32x4 w = gained(load(k), k);
+    const f32x4 w = row.gained(row.load(k), k);
     uint16_t h[4], l[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const float v = ldexpf(w[i], e);
       const _Float16 vh = (_Float16)v;
+      const float rest = v - (float)vh;
       h[i] = __builtin_bit_cast(uint16_t, vh);
-      l[i] = __builtin_bit_cast(uint16_t, (_Float16)(fabsf(v) < INFINITY ? v - (float)vh : 0.f));
+      l[i] = __builtin_bit_cast(uint16_t, (_Float16)rest);
+      lost += PARTS == 1 ? rest != 0.f : fabsf(v) < 0.25f && v != 0.f;
     }
     hi[k] = uint2{h[0] | ((uint32_t)h[1] << 16), h[2] | ((uint32_t)h[3] << 16)};
     if (PARTS == 2) lo[k] = uint2{l[0] | ((uint32_t)l[1] << 16), l[2] | ((uint32_t)l[3] << 16)};
   }
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) lost += __shfl_xor(lost, o);
+  __shared__ int rl[4];
+  if ((tid & 63) == 0) rl[tid >> 6] = lost;
+  __syncthreads();
+  lost = rl[0] + rl[1] + rl[2] + rl[3];
+  if (lost > (PARTS == 1 ? 0 : H / 8)) {
+    if (tid == 0) wide[r] = e;
+    zeros();
+  }
+}
+
+// Logits of the chunk's rows that head_rows_kernel left out, in fp32.  Such rows are the
+// exception: the launch ends at once where there are none (5 us) and is otherwise bound
+// by the stream of the matrix, four rows a pass (8B head: 270 to 290 us).  A wave takes
+// four columns at a time, so that the rows' values, which come from the caches, serve four of
+// the matrix's; eight products are added pairwise, and a lane adds K / 512 of these.
+__global__ __launch_bounds__(256) void head_wide_rows_kernel(const void* in, int in_bf16, const uint16_t* gain,
+                                                             const uint16_t* w, int rows, int N, int H,
+                                                             const double* row_scale, const int* wide, float* logits,
+                                                             int* err_flag) {
+  __shared__ int list[2 * kHeadChunk], count;
+  const int tid = threadIdx.x, lane = tid & 63;
+  if (tid == 0) count = 0;
+  __syncthreads();
+  for (int r = tid; r < rows; r += 256)
+    if (wide[r] != kHeld) list[atomicAdd(&count, 1)] = r;
+  __syncthreads();
+  const int n = count;
+  constexpr int R = 4, C = 4;
+  bool nan = false;
+  for (int i0 = 0; i0 < n; i0 += R) {
+    HeadRow row[R];
+    int e[R];
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+      const int r = list[min(i0 + i, n - 1)];
+      row[i] = HeadRow{in, in_bf16, gain, (int64_t)r * (H / 4)};
+      e[i] = wide[r];
+    }
+    for (int c0 = C * (4 * (int)blockIdx.x + (tid >> 6)); c0 < N; c0 += C * 4 * gridDim.x) {
+      float sum[C][R] = {};
+      for (int k = lane; k < H / 8; k += 64) {
+        h8 wk[C];
+#pragma unroll
+        for (int c = 0; c < C; ++c)
+          wk[c] = reinterpret_cast<const h8*>(w + (int64_t)min(c0 + c, N - 1) * H)[k];
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+          const f32x4 a = row[i].gained(row[i].load(2 * k), 2 * k), b = row[i].gained(row[i].load(2 * k + 1), 2 * k + 1);
+          float x[8];
+#pragma unroll
+          for (int j = 0; j < 8; ++j) x[j] = ldexpf(j < 4 ? a[j] : b[j - 4], e[i]);
+#pragma unroll
+          for (int c = 0; c < C; ++c) {
+            float p[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) p[j] = fmaf((float)wk[c][2 * j], x[2 * j], (float)wk[c][2 * j + 1] * x[2 * j + 1]);
+            sum[c][i] += (p[0] + p[1]) + (p[2] + p[3]);
+          }
+        }
+      }
+#pragma unroll
+      for (int c = 0; c < C; ++c)
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+          float t = sum[c][i];
+#pragma unroll
+          for (int o = 32; o >= 1; o >>= 1) t += __shfl_xor(t, o);
+          if (lane == 0 && i0 + i < n && c0 + c < N) {
+            const int r = list[i0 + i];
+            const float y = (float)((double)t * row_scale[r]);
+            nan |= y != y;
+            logits[(int64_t)r * N + c0 + c] = y;
+          }
+        }
+    }
+  }
+  raise_err(err_flag, nan, kErrNaNLogit);
 }
 
 // Order of the logits' K steps, the same in every tile and kernel: equal rows of
@@ -761,7 +857,7 @@ static int logits_kstride(int nk) {
 
 // K steps that an accumulator of the logits runs over: as many as leave the error of
 // fp32 rows at the GEMV's (K = 4096: 1.2e-7 each, and 1.0e-7 with one step; bf16 rows
-// 0.8e-7 against 1.0e-7).  Each fold costs 4 vector instructions a value: 256 fp32
+// 0.8e-7 against 1.0e-7).  Each fold costs 3 vector instructions a value: 256 fp32
 // rows of the 8B head 521 us without folds, 570 with one every two steps, 660 with one
 // every step.  A short K affords the latter (K = 320: 1.0e-7 each).
 static int logits_fold(int nk) { return nk < 32 ? 1 : 2; }
@@ -771,20 +867,25 @@ hipError_t launch_head_logits(const void* in, int in_bf16, const uint16_t* gain,
                               hipStream_t s, int tile) {
   const int parts = in_bf16 && !gain ? 1 : 2;
   if (rows <= 0 || rows > kHeadChunk * 2 / parts || N <= 0 || K <= 0 || K % BK) return hipErrorInvalidValue;
+  int* wide = reinterpret_cast<int*>(row_scale + 2 * kHeadChunk);
   const int blocks = (rows + 31) / 32, epi = parts == 1 ? kGemmLogits : kGemmLogitsSplit;
   if (parts == 1)
     hipLaunchKernelGGL(head_rows_kernel<1>, dim3(32 * blocks), dim3(256), 0, s, in, in_bf16, gain, rows, K, eps, a,
-                       row_scale);
+                       row_scale, wide);
   else
     hipLaunchKernelGGL(head_rows_kernel<2>, dim3(32 * blocks), dim3(256), 0, s, in, in_bf16, gain, rows, K, eps, a,
-                       row_scale);
-  const hipError_t e = hipGetLastError();
+                       row_scale, wide);
+  hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const int M = 32 * blocks * parts;
   const Params p{a, w, nullptr, M, N, K, 1, logits, nullptr, err_flag, rows, row_scale, logits_kstride(K / BK),
                  logits_fold(K / BK)};
   if (tile < 0) tile = gemm_plan(epi, M, N, K, 0).tile;
-  return parts == 1 ? launch_tile<kGemmLogits>(p, tile, s) : launch_tile<kGemmLogitsSplit>(p, tile, s);
+  e = parts == 1 ? launch_tile<kGemmLogits>(p, tile, s) : launch_tile<kGemmLogitsSplit>(p, tile, s);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(head_wide_rows_kernel, dim3(min(1024, (N + 15) / 16)), dim3(256), 0, s, in, in_bf16, gain, w, rows,
+                     N, K, row_scale, wide, logits, err_flag);
+  return hipGetLastError();
 }
 
 }  // namespace kf

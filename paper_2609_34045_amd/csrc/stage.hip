@@ -131,7 +131,7 @@ struct kf_stage {
   int* part_idx = nullptr;
   // logits of many rows (head_reserve): a chunk's rows as matrix operands
   uint16_t* head_a = nullptr;
-  double* head_scale = nullptr;   // and the factor of each of its rows
+  double* head_scale = nullptr;   // and, kHeadScaleBytes, what brings the rows back
   int lm_wg = 0;       // capacity of the argmax partials per batch row
   int lm_wg_used = 0;  // partials per row written by the last LM-head launch
   int kept_rows = 0;   // rows the last decode kept for the head (called without hidden output), else 0
@@ -1146,7 +1146,7 @@ static bool head_reserve(kf_stage* s) {
   // Relaxed: the allocation leaves captures of other threads alone.
   hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
   (void)hipThreadExchangeStreamCaptureMode(&mode);
-  const hipError_t e = hipMalloc((void**)&mem, a + rows * sizeof(double));
+  const hipError_t e = hipMalloc((void**)&mem, a + kHeadScaleBytes);
   (void)hipThreadExchangeStreamCaptureMode(&mode);
   if (e != hipSuccess) {
     (void)hipGetLastError();

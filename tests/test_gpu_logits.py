@@ -108,6 +108,35 @@ def test_sums_as_exact_as_the_gemv(torch, st, rows, io, limit):
     g.close()
 
 
+@pytest.mark.parametrize("io", ["float32", "bfloat16"])
+@pytest.mark.parametrize("rows", [5, 40, 300])
+def test_rows_of_wide_range(torch, st, rows, io):
+    """Rows with one value 2^20 or 2^40 times the others, and rows spread over ten decades, among ordinary ones.  In every other
+    LM-head row that value's weight is zero, so its logits rest on the small values alone: each row's error there
+    against 64-bit sums stays at the GEMV's (as above; a fixed number of bits below the largest value gives 2e-6 and
+    more)."""
+    def edit(head):
+        head["lm_head"][::2, 11] = 0
+
+    hidden = 1024
+    shape, head, g = head_stage(st, hidden, 777, 87, edit)
+    gain, w = ((head[k].astype(np.uint32) << 16).view(np.float32) for k in ("final_norm", "lm_head"))
+    rng = np.random.default_rng(87)
+    x = rng.standard_normal((rows, hidden))
+    x[1, 11], x[rows - 1, 11] = 2.0 ** 20, -2.0 ** 40
+    x[rows // 2::9] *= 10 ** rng.uniform(-10, 0, x[rows // 2::9].shape)
+    x = torch.from_numpy(x.astype(np.float32)).to(getattr(torch, io))
+    xd = x.double().numpy()
+    ref = (xd / np.sqrt(np.mean(xd * xd, axis=1, keepdims=True) + shape.rms_eps)) @ (w * gain).astype(np.float16).astype(np.float64).T
+    y = host(g.head_logits(x.cuda()))
+    for cols in (slice(0, None, 2), slice(1, None, 2)):
+        err = np.linalg.norm((y - ref)[:, cols], axis=1) / np.linalg.norm(ref[:, cols], axis=1)
+        print(f"{rows} {io}: largest row error {err.max():.2e}")
+        assert err.max() <= 2.5e-7, (int(err.argmax()), err.max())  # a row's error varies more than that of many rows
+    g.sync()
+    g.close()
+
+
 def test_first_call_under_capture(torch, st):
     """Nine rows as a stage's first call of more than four, while its stream is being captured: four at a time, without
     the workspace; after an eager call a capture takes the many-row path.  Both graphs replayed among eager work."""
