@@ -287,7 +287,9 @@ kf_status kf_stage_decode(kf_stage* stage, kf_kv* kv, int32_t batch, const int32
  * slots 0..pos0+i.  tokens_dev int32 [n] or hidden_in_dev [n, H]; hidden_out_dev [n, H].
  * A paged cache lends the pages up to pos0 + n (KF_ENOMEM if it cannot).
  * Dense products run on the matrix cores with fp16 operands (the stage's fp16 weights)
- * and fp32 accumulation.
+ * and fp32 accumulation.  The stage's workspace grows to the longest chunk; where the device has not
+ * the memory for all the partial sums that would be fastest, the sums are split less (the last
+ * bits of the results may differ), and KF_ENOMEM only where the chunk does not fit at all.
  * On success the user's length advances by n_tokens.
  */
 kf_status kf_stage_prefill(kf_stage* stage, kf_kv* kv, int32_t user, int32_t pos0, int32_t n_tokens,

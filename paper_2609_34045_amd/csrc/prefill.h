@@ -65,6 +65,7 @@ hipError_t launch_head_logits(const void* in, int in_bf16, const uint16_t* gain,
 // Device workspace, grown on demand to the largest chunk seen and laid out anew for each chunk.
 struct PrefillWorkspace {
   int64_t cap = 0;  // bytes at mem
+  bool refused = false;  // the device had not the memory for more
   char* mem = nullptr;
   float* x = nullptr;      // [T][H] residual stream
   uint16_t* xn = nullptr;  // [T][H] normalised, fp16
@@ -81,14 +82,24 @@ struct PrefillWorkspace {
 // Bytes of the no-allocation prefill's scratch array (a 512-token chunk of the 70B shape needs 132 MiB).
 constexpr int64_t kPrefillScratchBytes = 144LL << 20;
 
-// Grows ws (hipMalloc) to hold a chunk of a.T tokens and lays it out.
-hipError_t prefill_reserve(PrefillWorkspace& ws, const PrefillArgs& a);
+// Device bytes for a chunk of a.T tokens: what it needs at least, the same for shorter ones
+// too, what the plans of all of these would use, and what its own plan would.
+struct PrefillSizes {
+  int64_t least, shorter, full, own;
+};
+PrefillSizes prefill_sizes(const PrefillArgs& a);
+// Drains the stream (its work may still use the buffer to be replaced) and allocates;
+// hipErrorOutOfMemory where the device has not the memory.
+hipError_t prefill_grow(void** mem, int64_t bytes, hipStream_t s);
+// Grows ws to hold a chunk of a.T tokens, and those of fewer, and lays it out for this one; with
+// less room for partial sums, and so fewer slices, where the device has not the memory for all.
+hipError_t prefill_reserve(PrefillWorkspace& ws, const PrefillArgs& a,
+                           hipError_t (*grow)(void** mem, int64_t bytes, hipStream_t s) = prefill_grow);
 void prefill_free(PrefillWorkspace& ws);
-// Device bytes a chunk of a.T tokens needs at least; a chunk that needs no more than
-// kPrefillScratchBytes can be laid out in that many bytes at `base` (256-byte
-// aligned; ws does not own them).
+// Device bytes a chunk of a.T tokens needs at least; a chunk that needs no more can be laid
+// out in `bytes` at `base` (256-byte aligned; ws does not own them).
 int64_t prefill_ws_bytes(const PrefillArgs& a);
-void prefill_carve(PrefillWorkspace& ws, char* base, const PrefillArgs& a);
+void prefill_carve(PrefillWorkspace& ws, char* base, int64_t bytes, const PrefillArgs& a);
 hipError_t prefill_layer(PrefillWorkspace& ws, const PrefillArgs& a, const PrefillLayer& l, const Tracer& tr);
 
 }  // namespace kf

@@ -846,7 +846,7 @@ static int attn_splits(const PrefillArgs& a, int64_t part_elems) {
   return best;
 }
 
-void prefill_carve(PrefillWorkspace& ws, char* base, const PrefillArgs& a) {
+void prefill_carve(PrefillWorkspace& ws, char* base, int64_t bytes, const PrefillArgs& a) {
   int64_t sz[5];
   other_sizes(a, sz);
   char* p = base;
@@ -861,7 +861,7 @@ void prefill_carve(PrefillWorkspace& ws, char* base, const PrefillArgs& a) {
   ws.act = (uint16_t*)p;
   p += sz[4];
   ws.part = (float*)p;
-  ws.part_elems = part_bytes(a) / 4;
+  ws.part_elems = std::min(part_bytes(a), bytes - (p - base)) / 4;
   ws.pending = 0;
   ws.qkv = gemm_plan(kGemmPartialF32, a.T, (a.nq + 2 * a.nkv) * a.hd, a.H, ws.part_elems);
   ws.oproj = gemm_plan(kGemmPartialF32, a.T, a.H, a.nq * a.hd, ws.part_elems);
@@ -870,30 +870,54 @@ void prefill_carve(PrefillWorkspace& ws, char* base, const PrefillArgs& a) {
   ws.down = gemm_plan(kGemmPartialF32, a.T, a.H, a.F, ws.part_elems);
 }
 
-hipError_t prefill_reserve(PrefillWorkspace& ws, const PrefillArgs& a) {
+PrefillSizes prefill_sizes(const PrefillArgs& a) {
   // A shorter chunk must fit too (a caller may capture one after a longer one
   // has run).  Its other buffers are smaller; its partial sums may not be: the
   // slices grow where fewer tokens make fewer row tiles, most at the end of
   // each 256-token tile.
-  int64_t part = part_bytes(a);
+  PrefillSizes z{prefill_ws_bytes(a), 0, 0, other_bytes(a) + part_bytes(a)};
+  int64_t sized = sized_part(a, a.T), part = part_bytes(a);
   PrefillArgs b = a;
-  for (b.T = 256; b.T < a.T; b.T += 256) part = std::max(part, part_bytes(b));
-  const int64_t total = other_bytes(a) + std::max(part, std::min(kPartSmall, a256(most_part(a) * 4)));
-  if (total > ws.cap) {
-    char* mem = nullptr;
-    // Drain work that may still use the old buffer before freeing it.
-    hipError_t e = hipStreamSynchronize(a.stream);
-    if (e != hipSuccess) return e;
-    e = hipMalloc((void**)&mem, total);
-    if (e != hipSuccess) {
-      (void)hipGetLastError();
-      return hipErrorOutOfMemory;
-    }
-    prefill_free(ws);
-    ws.mem = mem;
-    ws.cap = total;
+  for (b.T = 256; b.T < a.T; b.T += 256) {
+    sized = std::max(sized, sized_part(b, b.T));
+    part = std::max(part, part_bytes(b));
   }
-  prefill_carve(ws, ws.mem, a);
+  z.shorter = other_bytes(a) + a256(sized * 4);
+  z.full = std::max(z.shorter, other_bytes(a) + std::max(part, std::min(kPartSmall, a256(most_part(a) * 4))));
+  return z;
+}
+
+hipError_t prefill_grow(void** mem, int64_t bytes, hipStream_t s) {
+  const hipError_t e = hipStreamSynchronize(s);
+  if (e != hipSuccess) return e;
+  if (hipMalloc(mem, bytes) == hipSuccess) return hipSuccess;
+  (void)hipGetLastError();
+  return hipErrorOutOfMemory;
+}
+
+hipError_t prefill_reserve(PrefillWorkspace& ws, const PrefillArgs& a,
+                           hipError_t (*grow)(void** mem, int64_t bytes, hipStream_t s)) {
+  const PrefillSizes z = prefill_sizes(a);
+  // Where the device had not the memory for the full size, later chunks (one of them may be
+  // under capture) take what there is until one needs more.
+  if (z.least > ws.cap || (z.full > ws.cap && !ws.refused)) {
+    bool refused = false;
+    for (const int64_t bytes : {z.full, z.shorter, z.least}) {
+      if (bytes <= ws.cap) break;  // no more than the buffer there is
+      void* mem = nullptr;
+      const hipError_t e = grow(&mem, bytes, a.stream);
+      if (e == hipSuccess) {
+        prefill_free(ws);
+        ws.mem = (char*)mem;
+        ws.cap = bytes;
+        break;
+      }
+      if (e != hipErrorOutOfMemory || bytes == z.least) return e;
+      refused = true;
+    }
+    ws.refused = refused;
+  }
+  prefill_carve(ws, ws.mem, ws.cap, a);
   return hipSuccess;
 }
 

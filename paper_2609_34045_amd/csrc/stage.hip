@@ -1252,7 +1252,7 @@ static kf_status prefill_impl(kf_stage* s, kf_kv* kv, int32_t user, int32_t pos0
       return fail(KF_ERANGE, "a chunk of %d tokens needs %lld bytes of prefill scratch, above the %lld held per device",
                   n, (long long)need, (long long)kPrefillScratchBytes);
     if (!s->scratch) return fail(KF_EDEVICE, "the device's prefill scratch has no address");
-    prefill_carve(scratch_ws, s->scratch, pa);
+    prefill_carve(scratch_ws, s->scratch, kPrefillScratchBytes, pa);
     ws = &scratch_ws;
   } else {
     hipError_t e = prefill_reserve(s->pf, pa);
