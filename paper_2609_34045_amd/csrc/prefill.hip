@@ -160,7 +160,7 @@ __global__ __launch_bounds__(BS) void rmsnorm_rows_f16_kernel(float* __restrict_
 }
 
 // ------------------------------------------------------------------ RoPE + KV append
-// QKV [T][(nq+2nkv) hd] fp32, the sum of nsplit split-K slices of `qkv` (slice
+// QKV [T][(nq+2nkv) hd] fp32, the sum of NS split-K slices of `qkv` (slice
 // stride `stride`) -> q [T][nq][hd] fp16 (rotated), K/V cache at pos0 + i (fp16).
 // A thread takes 4 consecutive rotation pairs (j .. j+3, j+hd/2 .. j+hd/2+3), one
 // item: grid.y covers a token's items, so that a few tokens fill the chip (with
@@ -169,7 +169,8 @@ __global__ __launch_bounds__(BS) void rmsnorm_rows_f16_kernel(float* __restrict_
 // With gq / gk set (blocks with per-head q / k norms), each q and k head is
 // RMS-normalised over its hd values first: the hd/8 consecutive threads that
 // hold a head add their squares with lane shuffles.
-__global__ __launch_bounds__(256) void rope_kv_kernel(const float* qkv, int nsplit, int64_t stride, uint16_t* q,
+template <int NS>
+__global__ __launch_bounds__(256) void rope_kv_kernel(const float* qkv, int64_t stride, uint16_t* q,
                                                       uint16_t* kc, uint16_t* vc, const KvPages kp, int user,
                                                       const float* cosT, const float* sinT, int nq, int nkv, int hd,
                                                       int pos0, const uint16_t* gq, const uint16_t* gk, float eps,
@@ -178,26 +179,26 @@ __global__ __launch_bounds__(256) void rope_kv_kernel(const float* qkv, int nspl
   const int nh = nq + 2 * nkv;
   const float* src = qkv + (int64_t)i * nh * hd;
   bool bad = false;
-  // A head's q4 threads, 8 or 16, are in one wave and in range together.  One
-  // pass: written as an `if`, the same body compiled to a kernel that took 17.2
-  // us against 7.4 (200 tokens, 5 slices).
-  for (int e = blockIdx.y * 256 + threadIdx.x; e < nh * q4; e += gridDim.y * 256) {
+  // A head's q4 threads, 8 or 16, are in one wave and in range together.  The number of
+  // slices is a constant: with a branch around each slice's loads the compiler
+  // may wait for one slice before it asks for the next (17.2 us against 7.4 for 200 tokens
+  // of 5 slices).
+  const int e = blockIdx.y * 256 + threadIdx.x;
+  if (e < nh * q4) {
     const int h = e / q4, j = (e % q4) * 4;
     v4f a = {0.f, 0.f, 0.f, 0.f}, b = {0.f, 0.f, 0.f, 0.f};
     {
-      v4f sa[kMaxSlices], sb[kMaxSlices];
+      v4f sa[NS], sb[NS];
 #pragma unroll
-      for (int sl = 0; sl < kMaxSlices; ++sl)
-        if (sl < nsplit) {
-          sa[sl] = *reinterpret_cast<const v4f*>(src + sl * stride + h * hd + j);
-          sb[sl] = *reinterpret_cast<const v4f*>(src + sl * stride + h * hd + j + half);
-        }
+      for (int sl = 0; sl < NS; ++sl) {
+        sa[sl] = *reinterpret_cast<const v4f*>(src + sl * stride + h * hd + j);
+        sb[sl] = *reinterpret_cast<const v4f*>(src + sl * stride + h * hd + j + half);
+      }
 #pragma unroll
-      for (int sl = 0; sl < kMaxSlices; ++sl)
-        if (sl < nsplit) {
-          a += sa[sl];
-          b += sb[sl];
-        }
+      for (int sl = 0; sl < NS; ++sl) {
+        a += sa[sl];
+        b += sb[sl];
+      }
     }
     uint16_t* dst;
     v4f z1, z2;
@@ -952,6 +953,28 @@ static hipError_t launch_rmsnorm(PrefillWorkspace& ws, const PrefillArgs& a, int
   }
 }
 
+template <int NS>
+static hipError_t launch_rope_kv_ns(PrefillWorkspace& ws, const PrefillArgs& a, const PrefillLayer& l) {
+  const int nh = a.nq + 2 * a.nkv;
+  hipLaunchKernelGGL(rope_kv_kernel<NS>, dim3(a.T, (nh * (a.hd / 8) + 255) / 256), dim3(256), 0, a.stream, ws.part,
+                     (int64_t)a.T * nh * a.hd, ws.q, l.kc, l.vc, a.kv, a.user, a.rope_cos, a.rope_sin, a.nq, a.nkv,
+                     a.hd, a.pos0, l.g_qn, l.g_kn, a.eps, a.err_flag);
+  return hipGetLastError();
+}
+static hipError_t launch_rope_kv(PrefillWorkspace& ws, const PrefillArgs& a, const PrefillLayer& l) {
+  switch (ws.qkv.slices) {
+    case 1: return launch_rope_kv_ns<1>(ws, a, l);
+    case 2: return launch_rope_kv_ns<2>(ws, a, l);
+    case 3: return launch_rope_kv_ns<3>(ws, a, l);
+    case 4: return launch_rope_kv_ns<4>(ws, a, l);
+    case 5: return launch_rope_kv_ns<5>(ws, a, l);
+    case 6: return launch_rope_kv_ns<6>(ws, a, l);
+    case 7: return launch_rope_kv_ns<7>(ws, a, l);
+    case 8: return launch_rope_kv_ns<8>(ws, a, l);
+    default: return hipErrorInvalidValue;
+  }
+}
+
 hipError_t prefill_layer(PrefillWorkspace& ws, const PrefillArgs& a, const PrefillLayer& l, const Tracer& tr) {
   hipStream_t s = a.stream;
   const int T = a.T, H = a.H, nqkv = (a.nq + 2 * a.nkv) * a.hd;
@@ -971,11 +994,9 @@ hipError_t prefill_layer(PrefillWorkspace& ws, const PrefillArgs& a, const Prefi
   tr.end(QKV);
   if (e != hipSuccess) return e;
   tr.begin(ROPE);
-  hipLaunchKernelGGL(rope_kv_kernel, dim3(T, ((a.nq + 2 * a.nkv) * (a.hd / 8) + 255) / 256), dim3(256), 0, s, ws.part, ws.qkv.slices, (int64_t)T * nqkv, ws.q, l.kc, l.vc,
-                     a.kv, a.user, a.rope_cos, a.rope_sin, a.nq, a.nkv, a.hd, a.pos0, l.g_qn, l.g_kn, a.eps,
-                     a.err_flag);
+  e = launch_rope_kv(ws, a, l);
   tr.end(ROPE);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
+  if (e != hipSuccess) return e;
   const float sl2 = (float)(1.4426950408889634 / std::sqrt((double)a.hd));
   const int Z = ws.attn_z;
   const dim3 ag((unsigned)(((int64_t)T * (a.nq / a.nkv) + 127) / 128), a.nkv, Z);
