@@ -3,7 +3,11 @@ test's choice (csrc/prefill.h declares them; the mangled names are the C++ ABI's
 import ctypes
 
 RESID, SWIGLU, PARTIAL, LOGITS, LOGITS_SPLIT = 1, 2, 3, 4, 5  # GemmEpi
-TILES = 9  # kTiles
+# kTiles: rows and columns
+TILES = [(32, 128), (64, 128), (128, 128), (128, 256), (128, 256), (256, 128), (256, 160), (256, 224), (256, 256)]
+# those that are built for an epilogue (has_tile)
+BUILT = {RESID: range(9), SWIGLU: range(9), PARTIAL: range(9), LOGITS: range(6), LOGITS_SPLIT: range(1, 9)}
+HEAD_CHUNK = 256  # kHeadChunk
 MAX_SLICES = 8  # kGemmMaxSlices
 
 
@@ -24,3 +28,12 @@ def launch_gemm(lib, epi, tile, slices, a, w, w2, m, n, k, c, cb, err, stream):
     f.restype, f.argtypes = ctypes.c_int, [ctypes.c_int, ctypes.POINTER(Plan), p, p, p] + [ctypes.c_int] * 3 + [p] * 4
     at = lambda t: None if t is None else t.data_ptr()  # noqa: E731
     return f(epi, ctypes.byref(Plan(tile, slices)), at(a), at(w), at(w2), m, n, k, at(c), at(cb), at(err), stream)
+
+
+def launch_head_logits(lib, x, gain, w, rows, n, k, eps, a, scale, y, err, stream, tile=-1):
+    """hipError_t of kf::launch_head_logits: x fp32 or bf16 rows, a [2 HEAD_CHUNK][k] fp16, scale 12 bytes a row of a."""
+    f = lib._ZN2kf18launch_head_logitsEPKviPKtS3_iiifPtPdPfPiP12ihipStream_ti
+    p, i = ctypes.c_void_p, ctypes.c_int
+    f.restype, f.argtypes = i, [p, i, p, p, i, i, i, ctypes.c_float, p, p, p, p, p, i]
+    at = lambda t: None if t is None else t.data_ptr()  # noqa: E731
+    return f(at(x), x.element_size() == 2, at(gain), at(w), rows, n, k, eps, at(a), at(scale), at(y), at(err), stream, tile)
