@@ -581,8 +581,10 @@ constexpr bool has_tile(int epi, int t) {
 // residual) at 5 TB/s.  At most eight slices (the consumers
 // add no more), of at least four steps, and no more than part_elems holds.
 // Over eighteen projections of the shapes above at eleven row counts from 20 to
-// 2048 the choice is the fastest of all tiles and slices or within 8% of it, bar
-// one (8192 x 8192 at 20 rows, 16%).
+// 2048 (198 products, two runs) the choice is the fastest of all tiles and slices or
+// within 8% of it in 195 and 190, and 16% off at worst (8192 x 8192 at 20 rows);
+// most of the misses are output and down projections at 200 rows, where the model
+// favours one or two slices too many (5120 x 5120: 33.1 us against 30.4).
 GemmPlan gemm_plan(int epi, int M, int N, int K, int64_t part_elems) {
   GemmPlan best{kTileCount - 1, 1};
   float best_us = 0.f;
@@ -838,9 +840,9 @@ __global__ __launch_bounds__(256) void head_wide_rows_kernel(const void* in, int
 // is the caller's to find) and a row the same bits however many rows are asked
 // for.  A stride of a quarter of the steps and one: the loads in flight spread
 // over a row, where all workgroups in natural order press on a few memory
-// channels (8B head, 5 and 64 fp32 rows: 217 and 245 us in natural order, 175
-// and 204 so; 164 and 203 with a start of its own for each tile; strides of 5 to
-// 33 steps of the 64 were no faster than 17).
+// channels (8B head, 5 and 64 fp32 rows, before sums were folded: 217 and 245 us in natural
+// order, 175 and 204 so; 164 and 203 with a start of its own for each tile; strides of 5
+// to 33 steps of the 64 were no faster than 17).
 static int logits_kstride(int nk) {
   int s = nk > 4 ? nk / 4 + 1 : 1;
   auto gcd = [](int a, int b) {

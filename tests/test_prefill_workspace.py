@@ -1,10 +1,11 @@
-"""The prefill workspace's sizes and its growth, on the host (csrc/prefill.h declares the entry points; the mangled
+"""The launch plans, the prefill workspace's sizes and its growth, on the host (csrc/prefill.h declares the entry points; the mangled
 names are the C++ ABI's).  Nothing here touches a device: allocations are the test's own."""
 import ctypes
 
 import pytest
 
 import synth
+from tests import gemm_calls as gc
 from tests.gemm_calls import Plan
 
 I64, P = ctypes.c_int64, ctypes.c_void_p
@@ -102,3 +103,11 @@ def test_a_chunk_runs_in_the_least_memory(lib, name, T):
             if lib.sizes(b).least <= ws.cap:
                 assert reserve(lib, ws, b, 0) == (0, []), (memory, t)
                 check(lib, ws, b)
+
+
+@pytest.mark.parametrize("epi", [gc.RESID, gc.SWIGLU, gc.PARTIAL, gc.LOGITS, gc.LOGITS_SPLIT])
+def test_the_plan_takes_only_tiles_that_are_built(lib, epi):
+    for m in range(32, 513, 32):
+        for n, k in ((64, 64), (777, 320), (128256, 4096), (151936, 5120)):
+            p = gc.plan(lib, epi, m, n, k, 8 * m * n)
+            assert p.tile in gc.BUILT[epi] and 1 <= p.slices <= gc.MAX_SLICES, (m, n, k)
