@@ -88,10 +88,15 @@ struct Params {
   float* C;
   uint16_t* Cb;
   int* err_flag;
-  int rows_out;            // logits: rows of the output (M counts the rows of A)
-  const double* row_scale;  // logits: the factor of each output row
-  int kstride;             // logits: K steps are taken in the order 0, kstride, 2 kstride, .. (mod their number)
-  int fold;                // logits: K steps that an accumulator runs over (Accum)
+  // logits only:
+  int rows_out;             // rows of the output (M counts the rows of A)
+  const double* row_scale;  // factor of each output row; its sign is set for the rows of wide_rows
+  int kstride;              // K steps are taken in the order 0, kstride, 2 kstride, .. (mod their number)
+  int fold;                 // K steps that an accumulator runs over (Accum)
+  const void* in;           // the rows themselves, fp32 or (in_bf16) bf16, the gain that is not folded into W,
+  int in_bf16;              // and the exponent that scales each row (head_rows_kernel)
+  const uint16_t* gain;
+  const int* row_exp;
 };
 
 // Rows of A per output row: the logits of fp32 rows take each row as two fp16
@@ -104,7 +109,7 @@ constexpr bool is_logits(int epi) { return epi == kGemmLogits || epi == kGemmLog
 template <int EPI, int MB, int JW>
 struct Accum {
   f32x16 acc[MB][JW] = {};
-  __device__ __forceinline__ void begin_step(int, const Params&) {}
+  __device__ __forceinline__ void begin_step(const Params&) {}
 };
 
 // Those of the logits.  A matrix instruction rounds into its accumulator twice, so
@@ -115,8 +120,10 @@ struct Accum {
 template <int MB, int JW>
 struct LogitAccum {
   f32x16 acc[MB][JW] = {}, sum[MB][JW] = {};
-  __device__ __forceinline__ void begin_step(int k, const Params& p) {
-    if (k % p.fold) return;
+  int left = 0;  // steps until the next fold
+  __device__ __forceinline__ void begin_step(const Params& p) {
+    if (left-- > 0) return;
+    left = p.fold - 1;
 #pragma unroll
     for (int i = 0; i < MB; ++i)
 #pragma unroll
@@ -124,7 +131,7 @@ struct LogitAccum {
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
           const float s = sum[i][j][v], a = acc[i][j][v], t = s + a;
-          acc[i][j][v] = a - (t - s);  // (no infinities here: head_wide_rows_kernel takes their rows)
+          acc[i][j][v] = a - (t - s);  // (no infinities here: wide_rows takes their rows)
           sum[i][j][v] = t;
         }
   }
@@ -144,6 +151,83 @@ constexpr int ring_a(int TM, int NB) { return TM == 256 && NB >= 7 ? 2 : 3; }
 constexpr int ring_w(int NB) { return NB == 4 ? 4 : 3; }
 constexpr int a_stage(int TM) { return TM * ROW_BYTES; }
 constexpr int w_stage(int NB) { return 32 * NB * ROW_BYTES; }
+
+// Logits of the rows that their fp16 parts do not hold (head_rows_kernel), in fp32, by
+// the launch's workgroups past its tiles: wave `wave` of `waves`.  Such rows are the
+// exception: where there are none these workgroups end at once, beside the tiles' (a launch of
+// their own cost 3 to 5 us).  Otherwise they are bound by the stream of the matrix, four rows a
+// pass (8B head: 220 to 270 us).  A wave takes four columns at a time, so that the rows' values, which come from the
+// caches, serve four of the matrix's; eight products are added pairwise, and a lane adds
+// K / 512 of these.
+constexpr int kWideCols = 4, kWideWorkgroups = 256;
+__device__ __forceinline__ void wide_rows(const Params& p, int lane, int wave, int waves) {
+  constexpr int R = 4, C = kWideCols;
+  const int H = p.K, last = p.N;
+  bool nan = false;
+  for (int b = 0; b < p.rows_out; b += 64) {
+    uint64_t todo = __ballot(b + lane < p.rows_out && __builtin_signbit(p.row_scale[min(b + lane, p.rows_out - 1)]));
+    while (todo) {
+      int r[R], e[R];
+      const uint2* row[R];
+      int n = 0;
+#pragma unroll
+      for (int i = 0; i < R; ++i) {
+        r[i] = i && !todo ? r[i > 0 ? i - 1 : 0] : b + __builtin_ctzll(todo);
+        if (todo) ++n;
+        todo &= todo - (todo != 0);
+        e[i] = p.row_exp[r[i]];
+        row[i] = reinterpret_cast<const uint2*>(p.in) + (int64_t)r[i] * (p.in_bf16 ? H / 4 : H / 2);
+      }
+      for (int c0 = C * wave; c0 < last; c0 += C * waves) {
+        float sum[C][R] = {};
+        for (int k = lane; k < H / 8; k += 64) {
+          // every load before a use: a branch on the rows' type would wait for each row in turn
+          h8 wk[C];
+#pragma unroll
+          for (int c = 0; c < C; ++c) wk[c] = reinterpret_cast<const h8*>(p.W + (int64_t)min(c0 + c, last - 1) * H)[k];
+          uint2 raw[R][4];  // 8 values: 4 words of bf16 (twice), or 8 of fp32
+#pragma unroll
+          for (int i = 0; i < R; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) raw[i][j] = row[i][p.in_bf16 ? 2 * k + (j & 1) : 4 * k + j];
+          float g[8];
+#pragma unroll
+          for (int j = 0; j < 8; ++j) g[j] = p.gain ? __uint_as_float((uint32_t)p.gain[8 * k + j] << 16) : 1.f;
+#pragma unroll
+          for (int i = 0; i < R; ++i) {
+            float x[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+              const uint32_t half = j & 2 ? raw[i][j / 4].y : raw[i][j / 4].x, word = j & 1 ? raw[i][j / 2].y : raw[i][j / 2].x;
+              x[j] = ldexpf(__uint_as_float(p.in_bf16 ? (j & 1 ? half & 0xffff0000u : half << 16) : word) * g[j], e[i]);
+            }
+#pragma unroll
+            for (int c = 0; c < C; ++c) {
+              float q[4];
+#pragma unroll
+              for (int j = 0; j < 4; ++j) q[j] = fmaf((float)wk[c][2 * j], x[2 * j], (float)wk[c][2 * j + 1] * x[2 * j + 1]);
+              sum[c][i] += (q[0] + q[1]) + (q[2] + q[3]);
+            }
+          }
+        }
+#pragma unroll
+        for (int c = 0; c < C; ++c)
+#pragma unroll
+          for (int i = 0; i < R; ++i) {
+            float t = sum[c][i];
+#pragma unroll
+            for (int o = 32; o >= 1; o >>= 1) t += __shfl_xor(t, o);
+            if (lane == 0 && i < n && c0 + c < last) {
+              const float y = (float)((double)t * fabs(p.row_scale[r[i]]));
+              nan |= y != y;
+              p.C[(int64_t)r[i] * p.N + c0 + c] = y;
+            }
+          }
+      }
+    }
+  }
+  raise_err(p.err_flag, nan, kErrNaNLogit);
+}
 
 // Epilogue of one wave's accumulators: MB 32-row blocks from output row row0
 // times JW 32-column blocks from block bw0 of the tile at column n0.  Lane l
@@ -180,21 +264,31 @@ __device__ __forceinline__ void store_tile(const Params& p, const Accum<EPI, MB,
   } else if constexpr (is_logits(EPI)) {
     bool nan = false;
 #pragma unroll
-    for (int i = 0; i < MB; ++i)
+    for (int i = 0; i < MB; ++i) {
+      // every factor before the first is used (the tile's rows past the output lie in the array too)
+      double scale[16];
+#pragma unroll
+      for (int v = 0; v < 16; v += 2) {
+        const double2 two = *reinterpret_cast<const double2*>(p.row_scale + row0 + 32 * i + 8 * (v >> 2) + rq + (v & 3));
+        scale[v] = two.x;
+        scale[v + 1] = two.y;
+      }
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
+        if (row0 + 32 * i + 8 * (v >> 2) >= p.rows_out) break;
         const int row = row0 + 32 * i + 8 * (v >> 2) + rq + (v & 3);
-        if (row >= p.rows_out) continue;
-        const double scale = p.row_scale[row];
+        const bool skip = __builtin_signbit(scale[v]);
 #pragma unroll
         for (int j = 0; j < JW; ++j) {
           const int col = n0 + 32 * (bw0 + j) + rl;
-          if (col >= p.N) continue;
-          const float y = (float)(((double)sums.sum[i][j][v] + (double)acc[i][j][v]) * scale);
-          nan |= y != y;
-          p.C[(int64_t)row * p.N + col] = y;
+          const float y = (float)(((double)sums.sum[i][j][v] + (double)acc[i][j][v]) * scale[v]);
+          if (row < p.rows_out && col < p.N && !skip) {
+            nan |= y != y;
+            p.C[(int64_t)row * p.N + col] = y;
+          }
         }
       }
+    }
     raise_err(p.err_flag, nan, kErrNaNLogit);
   } else {
 #pragma unroll
@@ -306,7 +400,7 @@ __device__ __forceinline__ void gemm_wave(const Params& p, uint8_t* smem, const 
   for (int q = 0; q < RD; ++q) read_frag(0, 0, q, fa[0], fw[0]);
   static_assert(SS % 2 == 0, "a step starts with its fragments in buffer 0");
   for (int k = 0; k + 1 < nk; ++k) {
-    sums.begin_step(k, p);
+    sums.begin_step(p);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int s = 0; s + 1 < SS; ++s)
@@ -324,7 +418,7 @@ __device__ __forceinline__ void gemm_wave(const Params& p, uint8_t* smem, const 
   }
   {
     const int k = nk - 1;
-    sums.begin_step(k, p);
+    sums.begin_step(p);
 #pragma unroll
     for (int s = 0; s + 1 < SS; ++s)
       half(fa[s & 1], fw[s & 1], k, s + 1, fa[(s + 1) & 1], fw[(s + 1) & 1], false, 0, 0);
@@ -357,6 +451,9 @@ __global__ __launch_bounds__(64 * NW) void gemm_tile_kernel(const Params p) {
   constexpr int TN = 32 * NB;  // tile columns
   const int mt = (p.M + TM - 1) / TM, nt = (p.N + TN - 1) / TN, ntiles = mt * nt;
   const int nwg = ntiles * p.splitk;
+  if constexpr (is_logits(EPI)) {
+    if ((int)blockIdx.x >= nwg) return wide_rows(p, lane, NW * (blockIdx.x - nwg) + wave, NW * (gridDim.x - nwg));
+  }
   // Tiles sharing a weight panel (same column tile) go to the same XCD, where
   // they reuse it through that XCD's L2 (workgroups are dealt round-robin).
   int bid = blockIdx.x;
@@ -448,6 +545,10 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_rows_kernel(const Params p)
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int mt = (p.M + TM - 1) / TM;
   const int bid = blockIdx.x;
+  if constexpr (is_logits(EPI)) {
+    const int nwg = mt * ((p.N + TN - 1) / TN);
+    if (bid >= nwg) return wide_rows(p, lane, NWV * (bid - nwg) + wave, NWV * (gridDim.x - nwg));
+  }
   const int ks = bid % p.splitk, t = bid / p.splitk;
   const int m0 = (t % mt) * TM, n0 = (t / mt) * TN;
   const int K = p.K, nk_all = K / KS;
@@ -531,7 +632,6 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_rows_kernel(const Params p)
     block_barrier();
     if (k + D - 1 < nk) issue(k + D - 1);
     const uint8_t* st = smem + (k % D) * STAGE;
-    sums.begin_step(k, p);
 #pragma unroll
     for (int s = 0; s < KS / 16; ++s) {
       const int c = ((2 * s + kh) ^ f) * 16;
@@ -540,6 +640,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_rows_kernel(const Params p)
       for (int j = 0; j < JW; ++j) fw[j] = *reinterpret_cast<const v4u*>(st + woff[j] + c);
 #pragma unroll
       for (int i = 0; i < MBW; ++i) fa[i] = *reinterpret_cast<const v4u*>(st + aoff[i] + c);
+      if (s == 0) sums.begin_step(p);  // while the fragments are on their way
 #pragma unroll
       for (int i = 0; i < MBW; ++i)
 #pragma unroll
@@ -614,7 +715,9 @@ template <int EPI>
 static hipError_t launch_tile(const Params& p, int tile, hipStream_t s) {
   if (tile < 0 || tile >= kTileCount || !has_tile(EPI, tile)) return hipErrorInvalidValue;
   const Tile& T = kTiles[tile];
-  const dim3 grid((unsigned)((int64_t)((p.M + T.rows - 1) / T.rows) * ((p.N + T.cols - 1) / T.cols) * p.splitk));
+  const int64_t tiles = (int64_t)((p.M + T.rows - 1) / T.rows) * ((p.N + T.cols - 1) / T.cols) * p.splitk;
+  const int wide = is_logits(EPI) ? min(kWideWorkgroups, (p.N + 4 * kWideCols - 1) / (4 * kWideCols)) : 0;  // wide_rows
+  const dim3 grid((unsigned)(tiles + wide));
   switch (tile) {
     case 0:
       if constexpr (has_tile(EPI, 0)) hipLaunchKernelGGL((gemm_rows_kernel<EPI, 1, 1, 1, 4, 4>), grid, dim3(256), 0, s, p);
@@ -644,7 +747,7 @@ hipError_t launch_gemm(int epi, const GemmPlan& plan, const uint16_t* A, const u
   if (epi == kGemmSwiGLU && N % 32) return hipErrorInvalidValue;  // whole 16-output gate/up blocks
   // the nonlinearity and the residual update need complete sums: only the partial epilogue splits K
   if (epi != kGemmPartialF32 && plan.slices != 1) return hipErrorInvalidValue;
-  const Params p{A, W, W2, M, N, K, plan.slices, C, Cb, err_flag, 0, nullptr, 1, 1};
+  const Params p{A, W, W2, M, N, K, plan.slices, C, Cb, err_flag, 0, nullptr, 1, 1, nullptr, 0, nullptr, nullptr};
   switch (epi) {
     case kGemmResidF32: return launch_tile<kGemmResidF32>(p, plan.tile, s);
     case kGemmSwiGLU: return launch_tile<kGemmSwiGLU>(p, plan.tile, s);
@@ -663,12 +766,11 @@ hipError_t launch_gemm(int epi, const GemmPlan& plan, const uint16_t* A, const u
 // sums (1.2e-7 each, 8B head).  Rows of which that is not so, because the fp16 part of
 // a bf16 row is not exact, more than an eighth of an fp32 row's values are
 // that small or there is an infinity, are operands of zeros here and go through
-// head_wide_rows_kernel.  Row r's factor is 1 / rms(v) and the power of two back, in 64
+// wide_rows.  Row r's factor is 1 / rms(v) and the power of two back, in 64
 // bits (fp32 would not hold every such product, and its roundings, the same for a whole
 // row, were half of the logits' error).  One workgroup per row; rows past `rows` fill their block with zeros.
-constexpr int kHeld = 1 << 30;  // wide[r] of a row that its parts hold; else its exponent
 
-struct HeadRow {  // a row of the head's input; values 4 k .. + 3, times the gain
+struct HeadRow {  // a row of the head's input: values 4 k .. + 3, and these times the gain
   const void* in;
   int bf16;
   const uint16_t* gain;
@@ -693,7 +795,7 @@ struct HeadRow {  // a row of the head's input; values 4 k .. + 3, times the gai
 
 template <int PARTS>
 __global__ __launch_bounds__(256) void head_rows_kernel(const void* in, int in_bf16, const uint16_t* gain, int rows,
-                                                        int H, float eps, uint16_t* a, double* row_scale, int* wide) {
+                                                        int H, float eps, uint16_t* a, double* row_scale, int* row_exp) {
   const int r = blockIdx.x, tid = threadIdx.x;
   uint2* hi = reinterpret_cast<uint2*>(a + (int64_t)(PARTS * (r & ~31) + (r & 31)) * H);
   uint2* lo = reinterpret_cast<uint2*>(a + (int64_t)(PARTS * (r & ~31) + 32 + (r & 31)) * H);
@@ -733,106 +835,37 @@ __global__ __launch_bounds__(256) void head_rows_kernel(const void* in, int in_b
   // value, or its product with the gain) the finite values are brought there from the
   // largest fp32 can hold.  A sum of squares beyond fp32 makes the factor 0, as the GEMV has it.
   const int e = mx == 0.f ? 0 : mx < INFINITY ? 13 - ilogbf(mx) : 13 - 127;
-  if (tid == 0) {
-    row_scale[r] = (float)ss == INFINITY ? 0. : ldexp(1.0 / sqrt(ss / H + (double)eps), -e);
-    wide[r] = mx == INFINITY ? e : kHeld;
-  }
-  if (mx == INFINITY) return zeros();
-  int lost = 0;  // values that the parts hold to fewer bits
-  for (int k = tid; k < H / 4; k += 256) {
-    const f32x4 w = row.gained(row.load(k), k);
-    uint16_t h[4], l[4];
+  bool wide = mx == INFINITY;
+  if (!wide) {
+    int lost = 0;  // values that the parts hold to fewer bits
+    for (int k = tid; k < H / 4; k += 256) {
+      const f32x4 w = row.gained(row.load(k), k);
+      uint16_t h[4], l[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const float v = ldexpf(w[i], e);
-      const _Float16 vh = (_Float16)v;
-      const float rest = v - (float)vh;
-      h[i] = __builtin_bit_cast(uint16_t, vh);
-      l[i] = __builtin_bit_cast(uint16_t, (_Float16)rest);
-      lost += PARTS == 1 ? rest != 0.f : fabsf(v) < 0.25f && v != 0.f;
-    }
-    hi[k] = uint2{h[0] | ((uint32_t)h[1] << 16), h[2] | ((uint32_t)h[3] << 16)};
-    if (PARTS == 2) lo[k] = uint2{l[0] | ((uint32_t)l[1] << 16), l[2] | ((uint32_t)l[3] << 16)};
-  }
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) lost += __shfl_xor(lost, o);
-  __shared__ int rl[4];
-  if ((tid & 63) == 0) rl[tid >> 6] = lost;
-  __syncthreads();
-  lost = rl[0] + rl[1] + rl[2] + rl[3];
-  if (lost > (PARTS == 1 ? 0 : H / 8)) {
-    if (tid == 0) wide[r] = e;
-    zeros();
-  }
-}
-
-// Logits of the chunk's rows that head_rows_kernel left out, in fp32.  Such rows are the
-// exception: the launch ends at once where there are none (5 us) and is otherwise bound
-// by the stream of the matrix, four rows a pass (8B head: 270 to 290 us).  A wave takes
-// four columns at a time, so that the rows' values, which come from the caches, serve four of
-// the matrix's; eight products are added pairwise, and a lane adds K / 512 of these.
-__global__ __launch_bounds__(256) void head_wide_rows_kernel(const void* in, int in_bf16, const uint16_t* gain,
-                                                             const uint16_t* w, int rows, int N, int H,
-                                                             const double* row_scale, const int* wide, float* logits,
-                                                             int* err_flag) {
-  __shared__ int list[2 * kHeadChunk], count;
-  const int tid = threadIdx.x, lane = tid & 63;
-  if (tid == 0) count = 0;
-  __syncthreads();
-  for (int r = tid; r < rows; r += 256)
-    if (wide[r] != kHeld) list[atomicAdd(&count, 1)] = r;
-  __syncthreads();
-  const int n = count;
-  constexpr int R = 4, C = 4;
-  bool nan = false;
-  for (int i0 = 0; i0 < n; i0 += R) {
-    HeadRow row[R];
-    int e[R];
-#pragma unroll
-    for (int i = 0; i < R; ++i) {
-      const int r = list[min(i0 + i, n - 1)];
-      row[i] = HeadRow{in, in_bf16, gain, (int64_t)r * (H / 4)};
-      e[i] = wide[r];
-    }
-    for (int c0 = C * (4 * (int)blockIdx.x + (tid >> 6)); c0 < N; c0 += C * 4 * gridDim.x) {
-      float sum[C][R] = {};
-      for (int k = lane; k < H / 8; k += 64) {
-        h8 wk[C];
-#pragma unroll
-        for (int c = 0; c < C; ++c)
-          wk[c] = reinterpret_cast<const h8*>(w + (int64_t)min(c0 + c, N - 1) * H)[k];
-#pragma unroll
-        for (int i = 0; i < R; ++i) {
-          const f32x4 a = row[i].gained(row[i].load(2 * k), 2 * k), b = row[i].gained(row[i].load(2 * k + 1), 2 * k + 1);
-          float x[8];
-#pragma unroll
-          for (int j = 0; j < 8; ++j) x[j] = ldexpf(j < 4 ? a[j] : b[j - 4], e[i]);
-#pragma unroll
-          for (int c = 0; c < C; ++c) {
-            float p[4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) p[j] = fmaf((float)wk[c][2 * j], x[2 * j], (float)wk[c][2 * j + 1] * x[2 * j + 1]);
-            sum[c][i] += (p[0] + p[1]) + (p[2] + p[3]);
-          }
-        }
+      for (int i = 0; i < 4; ++i) {
+        const float v = ldexpf(w[i], e);
+        const _Float16 vh = (_Float16)v;
+        const float rest = v - (float)vh;
+        h[i] = __builtin_bit_cast(uint16_t, vh);
+        l[i] = __builtin_bit_cast(uint16_t, (_Float16)rest);
+        lost += PARTS == 1 ? rest != 0.f : fabsf(v) < 0.25f && v != 0.f;
       }
-#pragma unroll
-      for (int c = 0; c < C; ++c)
-#pragma unroll
-        for (int i = 0; i < R; ++i) {
-          float t = sum[c][i];
-#pragma unroll
-          for (int o = 32; o >= 1; o >>= 1) t += __shfl_xor(t, o);
-          if (lane == 0 && i0 + i < n && c0 + c < N) {
-            const int r = list[i0 + i];
-            const float y = (float)((double)t * row_scale[r]);
-            nan |= y != y;
-            logits[(int64_t)r * N + c0 + c] = y;
-          }
-        }
+      hi[k] = uint2{h[0] | ((uint32_t)h[1] << 16), h[2] | ((uint32_t)h[3] << 16)};
+      if (PARTS == 2) lo[k] = uint2{l[0] | ((uint32_t)l[1] << 16), l[2] | ((uint32_t)l[3] << 16)};
     }
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) lost += __shfl_xor(lost, o);
+    __shared__ int rl[4];
+    if ((tid & 63) == 0) rl[tid >> 6] = lost;
+    __syncthreads();
+    wide = rl[0] + rl[1] + rl[2] + rl[3] > (PARTS == 1 ? 0 : H / 8);
   }
-  raise_err(err_flag, nan, kErrNaNLogit);
+  if (wide) zeros();
+  if (tid == 0) {
+    const double scale = fabs((float)ss == INFINITY ? 0. : ldexp(1.0 / sqrt(ss / H + (double)eps), -e));
+    row_scale[r] = wide ? -scale : scale;
+    row_exp[r] = e;
+  }
 }
 
 // Order of the logits' K steps, the same in every tile and kernel: equal rows of
@@ -857,37 +890,33 @@ static int logits_kstride(int nk) {
   return s;
 }
 
-// K steps that an accumulator of the logits runs over: as many as leave the error of
-// fp32 rows at the GEMV's (K = 4096: 1.2e-7 each, and 1.0e-7 with one step; bf16 rows
-// 0.8e-7 against 1.0e-7).  Each fold costs 3 vector instructions a value: 256 fp32
-// rows of the 8B head 521 us without folds, 570 with one every two steps, 660 with one
-// every step.  A short K affords the latter (K = 320: 1.0e-7 each).
-static int logits_fold(int nk) { return nk < 32 ? 1 : 2; }
+// K steps that an accumulator of the logits runs over: as many as leave the error at the
+// GEMV's (K = 4096: fp32 rows 1.2e-7 each, and 1.1e-7 with one step; bf16 rows
+// 0.8e-7 against 1.0e-7; K = 320, fp32 rows: 1.0e-7 each with one step, 1.2e-7 with two).
+// Each fold costs 3 vector instructions a value: 256 fp32 rows of the 8B head 521 us
+// without folds, 560 with one every two steps, 660 with one every step.
+static int logits_fold(int parts, int nk) { return parts == 2 && nk < 32 ? 1 : 2; }
 
 hipError_t launch_head_logits(const void* in, int in_bf16, const uint16_t* gain, const uint16_t* w, int rows, int N,
                               int K, float eps, uint16_t* a, double* row_scale, float* logits, int* err_flag,
                               hipStream_t s, int tile) {
   const int parts = in_bf16 && !gain ? 1 : 2;
   if (rows <= 0 || rows > kHeadChunk * 2 / parts || N <= 0 || K <= 0 || K % BK) return hipErrorInvalidValue;
-  int* wide = reinterpret_cast<int*>(row_scale + 2 * kHeadChunk);
+  int* row_exp = reinterpret_cast<int*>(row_scale + 2 * kHeadChunk);
   const int blocks = (rows + 31) / 32, epi = parts == 1 ? kGemmLogits : kGemmLogitsSplit;
   if (parts == 1)
     hipLaunchKernelGGL(head_rows_kernel<1>, dim3(32 * blocks), dim3(256), 0, s, in, in_bf16, gain, rows, K, eps, a,
-                       row_scale, wide);
+                       row_scale, row_exp);
   else
     hipLaunchKernelGGL(head_rows_kernel<2>, dim3(32 * blocks), dim3(256), 0, s, in, in_bf16, gain, rows, K, eps, a,
-                       row_scale, wide);
-  hipError_t e = hipGetLastError();
+                       row_scale, row_exp);
+  const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const int M = 32 * blocks * parts;
   const Params p{a, w, nullptr, M, N, K, 1, logits, nullptr, err_flag, rows, row_scale, logits_kstride(K / BK),
-                 logits_fold(K / BK)};
+                 logits_fold(parts, K / BK), in, in_bf16, gain, row_exp};
   if (tile < 0) tile = gemm_plan(epi, M, N, K, 0).tile;
-  e = parts == 1 ? launch_tile<kGemmLogits>(p, tile, s) : launch_tile<kGemmLogitsSplit>(p, tile, s);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(head_wide_rows_kernel, dim3(min(1024, (N + 15) / 16)), dim3(256), 0, s, in, in_bf16, gain, w, rows,
-                     N, K, row_scale, wide, logits, err_flag);
-  return hipGetLastError();
+  return parts == 1 ? launch_tile<kGemmLogits>(p, tile, s) : launch_tile<kGemmLogitsSplit>(p, tile, s);
 }
 
 }  // namespace kf

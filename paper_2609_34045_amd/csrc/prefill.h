@@ -56,7 +56,7 @@ hipError_t launch_gemm(int epi, const GemmPlan& plan, const uint16_t* A, const u
 // Logits of many rows: logits[rows][N] = RMSNorm(in; gain) W^T on the matrix cores, for
 // up to kHeadChunk fp32 rows (2 kHeadChunk bf16 rows when gain is NULL, i.e. folded into W).
 // a: [2 kHeadChunk][K] fp16 and row_scale: kHeadScaleBytes are workspace; tile: one of kTiles, or -1 for the plan's.
-constexpr int kHeadChunk = 256;  // 8B head: a chunk of 256 fp32 rows takes 575 us, two of 128 rows 600
+constexpr int kHeadChunk = 256;  // 8B head: a chunk of 256 fp32 rows takes 550 us, two of 128 rows 600
 constexpr int kHeadScaleBytes = 2 * kHeadChunk * (sizeof(double) + sizeof(int));
 hipError_t launch_head_logits(const void* in, int in_bf16, const uint16_t* gain, const uint16_t* w, int rows, int N,
                               int K, float eps, uint16_t* a, double* row_scale, float* logits, int* err_flag,

@@ -1164,7 +1164,7 @@ kf_status kf_head_logits(kf_stage* s, int32_t rows, const void* hidden, kf_dtype
   if (!hidden) return head_launch(s, rows, nullptr, dtype, logits);  // kept rows: at most kMaxBatch
   if (rows <= kMaxBatch) return head_launch(s, rows, hidden, dtype, logits);
   // More rows than one GEMV pass over the matrix takes: chunks on the matrix
-  // cores (8B-shaped head, fp32: 256 rows 11,950 -> 578 us; 5 to 16 rows, two to
+  // cores (8B-shaped head, fp32: 256 rows 11,950 -> 565 us; 5 to 16 rows, two to
   // four passes of the GEMV of 187 us each before, 185 to 200 us, about one pass).
   const kf_model_config& c = s->cfg;
   const bool bf16 = dtype == KF_BF16;
