@@ -325,6 +325,8 @@ kf_status kf_stage_prefill_noalloc(kf_stage* stage, kf_kv* kv, int32_t user, int
  * use a workspace of 6 KB and 1 KB per hidden value, allocated at a stage's first such call and kept;
  * where it cannot be had (no device memory left, or that call is under HIP graph capture)
  * the rows go four at a time, in the order and at the cost of such calls.
+ * A row whose values two fp16 parts do not hold (more than an eighth of them far below its
+ * largest, or an infinity) is taken in fp32 all the same; such rows cost a pass over the LM head per four.
  * hidden_dev NULL: the rows the stage's last kf_stage_decode kept (its hidden_out_dev
  * was NULL); rows must equal that decode's batch and dtype is ignored (else KF_ESTATE,
  * also when the last decode returned its rows or failed).
